@@ -577,7 +577,7 @@ def main():
     oms = float(np.mean([e[0].elapsed_time(e[1]) for e in eo]))
     opt = {"ms": oms, "GBps": enc_bytes / (oms * 1e-3) / 1e9}
 
-    # the exact int8 contraction (a variant of the product, not part of the step)
+    # the int8 contraction asked for with its flag (the step takes it by itself where it fits)
     i8 = None
     if k * q <= 63:
         ev8 = [[torch.cuda.Event(enable_timing=True) for _ in range(3)] for _ in range(args.steps)]
@@ -611,26 +611,28 @@ def main():
     con_tflops = flops / (con_ms * 1e-3) / 1e12
     value = flops / (ms_per_step * 1e-3) / 1e12
     skinny = M <= 64
+    # the library takes int8 tiles and exact int32 sums where every m X2 fits (full decoder)
+    unit, peak = ("int8", INT8_PEAK_TOPS) if 2 * q * k <= 128 else ("bf16", BF16_PEAK_TFLOPS)
     if skinny:
         # decode-shaped product: the contraction kernel streams the coded W (HBM roofline)
         con_bytes = mm_bytes
         con_gbps = con_bytes / (con_ms * 1e-3) / 1e9
-        roofline = {"kernel": "skinny_kernel (W decoded into 16x16x32 bf16 MFMA operands)",
+        roofline = {"kernel": "skinny_kernel (W decoded into matrix-core operands)",
                     "bound": "hbm", "achieved": con_gbps, "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                     "frac": con_gbps / HBM_PEAK_GBPS, "traffic": None,
                     "per_launch": f"{con_bytes} algorithmic bytes (coded A, coded W, fp32 C)"}
     else:
-        roofline = {"kernel": "gemm_kernel (bf16 MFMA contraction of the decoded tiles)",
-                    "bound": "mfma", "achieved": con_tflops, "peak": BF16_PEAK_TFLOPS,
-                    "unit": "TFLOP/s", "frac": con_tflops / BF16_PEAK_TFLOPS,
+        roofline = {"kernel": f"gemm_kernel ({unit} MFMA contraction of the decoded tiles)",
+                    "bound": "mfma", "achieved": con_tflops, "peak": peak,
+                    "unit": "TFLOP/s", "frac": con_tflops / peak,
                     "traffic": gemm_traffic(cfg, q),
                     "per_launch": f"2*M*N*K = {flops:.4g} flops"}
     # the product from the codes as a whole (decode of both operands + contraction), the
     # quantity the decode-GEMM target is stated for
     decode_gemm = {"kernels": "operand decode + contraction (nq_matmul_stages)",
-                   "bound": "mfma", "achieved": mm_tflops, "peak": BF16_PEAK_TFLOPS,
-                   "unit": "TFLOP/s", "frac": mm_tflops / BF16_PEAK_TFLOPS,
-                   "median_frac": flops / (mm_t["median_ms"] * 1e-3) / 1e12 / BF16_PEAK_TFLOPS,
+                   "bound": "mfma", "achieved": mm_tflops, "peak": peak,
+                   "unit": "TFLOP/s", "frac": mm_tflops / peak,
+                   "median_frac": flops / (mm_t["median_ms"] * 1e-3) / 1e12 / peak,
                    "per_call": f"2*M*N*K = {flops:.4g} flops"}
     kv = None if args.no_kv else kv_measure(min(args.steps, 50), min(args.warmup, 20))
 
@@ -649,6 +651,7 @@ def main():
         "data": "synthetic",
         "config": {
             "workload": c["name"], "M": M, "N": N, "K": K, "q": q, "k": k,
+            "contraction": f"exact {unit} tiles" if unit == "int8" else "bf16 tiles",
             "A": f"{dta} {'Student-t(4)' if cfg == 3 else 'synthetic'}", "W": f"{dtw} coded once",
             "launch": "HIP graph replay of the step" if use_graph else "direct launches",
             "parallelism": "single GPU",

@@ -144,7 +144,11 @@ nq_status nq_matmul(const nq_params* pa, const uint32_t* a_codes, const uint32_t
 /* nq_matmul with a caller-owned device workspace (16-byte aligned, at least
  * nq_matmul_workspace_size(M, N, K) bytes): every block of both operands is decoded exactly
  * once (Alg. 2) into integer tiles m*X2 in the workspace (for M <= 64 only A's; W is then
- * decoded straight into matrix-core operands), then contracted.  Same product as nq_matmul
+ * decoded straight into matrix-core operands), then contracted.  The tiles are int8, with
+ * exact int32 sums on int8 matrix cores, when every m*X2 of both operands fits int8 (2q *
+ * mult_k <= 127, or 128 with NQ_DECODER_FULL, whose points have coordinates in [-2q, 2q - 1];
+ * so for q <= 15 on the uniform grid, and q = 16 with the full decoder), else bf16 or fp16
+ * as in nq_matmul.  Same product as nq_matmul
  * (for M <= 64 the fp32 sums are taken in another order).  With M <= 2 (and A's tile within
  * 48 KiB) the product kernel decodes A itself and the workspace is unused; there, when
  * every sum fits 32 bits (8 * ceil(K / 64) * 8 * (2 q_A)(2 q_W) * max mult_A * max mult_W
@@ -183,13 +187,14 @@ nq_status nq_matmul_static(const nq_params* pa, const uint32_t* a_codes, const u
  *                      M > 64, of W, as m*X2);
  *   NQ_STAGE_CONTRACT  computes C from the workspace (for M <= 64 it also decodes W, straight
  *                      into matrix-core operands);
- *   NQ_CONTRACT_INT8   stores m*X2 as int8 and contracts on int8 matrix cores with int32
- *                      accumulation instead of bf16 / fp32.  Every inner product
- *                      sum <m_A X2_A, m_W X2_W> (Alg. 4 without its scale) is then exact, and
- *                      C = fp32(sum) * r_A * r_W * base_A * base_W / 4.  It requires
- *                      2q * mult_k <= 127 for both operands (with the uniform grid: k * q <= 63;
- *                      |m X2| <= 2q m must fit int8), else NQ_ERR_UNSUPPORTED.  Both stages
- *                      of one product must agree on it.
+ *   NQ_CONTRACT_INT8   asks for int8 tiles and int8 matrix cores with int32 accumulation:
+ *                      every inner product sum <m_A X2_A, m_W X2_W> (Alg. 4 without its
+ *                      scale) is then exact, and C = fp32(sum) * r_A * r_W * base_A *
+ *                      base_W / 4.  It requires 2q * mult_k <= 127 for both operands (with
+ *                      the uniform grid: k * q <= 63), else NQ_ERR_UNSUPPORTED.  Without the
+ *                      flag the library takes the same tiles where they fit (nq_matmul_ex)
+ *                      and wider ones elsewhere.  Both stages of one product must agree on
+ *                      the flag.
  * A DECODE call followed by a CONTRACT call with the same arguments on the same stream is
  * exactly the call with both bits; DECODE | CONTRACT is nq_matmul_ex.  The workspace must
  * not change in between.  Arguments are validated as in nq_matmul_ex; any other bit, or no

@@ -212,7 +212,8 @@ def matmul(a, w, stream=None, out=None, workspace=None, stages=STAGE_DECODE | ST
     The decode-once workspace is taken from torch's allocator unless given.  ``stages``
     selects part of the call (nq_matmul_stages): STAGE_DECODE fills the workspace,
     STAGE_CONTRACT computes C from it; both (the default) is the whole product.  ``int8``
-    contracts exact int8 tiles on int8 matrix cores (needs k * q <= 63)."""
+    insists on exact int8 tiles and int8 matrix cores (needs k * q <= 63); without it the
+    library takes them by itself where every tile value fits."""
     import torch
     if a.cols != w.cols:
         raise ValueError("K mismatch")

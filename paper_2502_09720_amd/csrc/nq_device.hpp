@@ -417,10 +417,10 @@ __device__ __forceinline__ u32x4 decode_tile_16(uint32_t w, int m, int q, uint32
                pack16<F16>(val(xb, 0), val(xb, 1)), pack16<F16>(val(xb, 2), val(xb, 3))};
 }
 
-// m * X2 of one block as eight int8 (exact when 2 q m <= 127: |X2| <= 2q), the
-// coordinates in byte order.  The signed bytes X2 are multiplied in 16-bit lanes (even and
-// odd bytes apart); each product keeps its low byte, the two's-complement int8 of a value
-// in [-127, 127].
+// m * X2 of one block as eight int8 (exact when m X2 fits, see tiles_fit_i8), the coordinates
+// in byte order.  The signed bytes X2 are multiplied in 16-bit lanes (even and odd bytes
+// apart): the low byte of a product depends on the low bytes of its factors alone, so the
+// other byte of a lane needs no mask, and one v_perm gathers the four low bytes.
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 template <int DV = 0>
 __device__ __forceinline__ u32x2 decode_tile_i8(uint32_t w, int m, int q, uint32_t m2q) {
@@ -429,9 +429,9 @@ __device__ __forceinline__ u32x2 decode_tile_i8(uint32_t w, int m, int q, uint32
   const uint32_t mm = (uint32_t)m | ((uint32_t)m << 16);   // m in both halves
   auto mul8 = [&](uint32_t x) {
     const uint32_t s = x ^ 0x80808080u;                  // X2 as signed bytes
-    const uint32_t lo = pk_mul_lo_u16(s & 0x00FF00FFu, mm);
-    const uint32_t hi = pk_mul_lo_u16((s >> 8) & 0x00FF00FFu, mm);
-    return (lo & 0x00FF00FFu) | ((hi & 0x00FF00FFu) << 8);
+    const uint32_t lo = pk_mul_lo_u16(s, mm);            // low bytes: those of bytes 0 and 2
+    const uint32_t hi = pk_mul_lo_u16(s >> 8, mm);       // of bytes 1 and 3
+    return __builtin_amdgcn_perm(hi, lo, 0x06020400u);
   };
   return u32x2{mul8(xa), mul8(xb)};
 }

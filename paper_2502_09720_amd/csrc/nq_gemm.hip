@@ -7,12 +7,12 @@
 // exactly once:
 //
 //   1. tiles_pair_kernel (both operands in one launch; tiles_kernel for one): Alg. 2 on
-//      every code word; writes m * X2 (beta = m * base; with the uniform grid m = t and
-//      |m X2| <= 128, exact in bf16) as 8 bf16 into a K-contiguous workspace tile,
-//      zero-padded to the GEMM tile grid.  Beta sets with larger multiples
-//      use fp16 tiles (exact to 2048) and fp16 matrix cores at the same rate.  The
-//      workspace (a few tens of MB) stays in the 256 MB Infinity Cache.
-//   2. gemm_kernel: bf16 MFMA GEMM (C = T_A T_W^T, fp32 accumulation) with the epilogue
+//      every code word; writes m * X2 (beta = m * base) into a K-contiguous workspace tile,
+//      zero-padded to the GEMM tile grid: as int8 where every m X2 of both operands fits
+//      (tiles_fit_i8; the uniform grid up to q = 15, and q = 16 with the full decoder), else
+//      as bf16 (|m X2| <= 256) or fp16 (to 2048).  The workspace (a few tens of MB) stays in
+//      the 256 MB Infinity Cache.
+//   2. gemm_kernel: MFMA GEMM (C = T_A T_W^T; int32 or fp32 accumulation) with the epilogue
 //      C_ij = acc * r_Ai * r_Wj * base_A * base_W / 4.
 //
 // GEMM tiling (gfx950): a workgroup of NW = WM x WN waves owns a BM x BN tile of C; each
@@ -35,8 +35,8 @@
 namespace nq {
 
 namespace gemm {
-constexpr int BK = 64;     // workspace rows are padded to 64 bf16 / 128 int8 ...
-constexpr int BKB = kTileRowBytes;   // ... i.e. to whole 128-byte runs (the largest stage row)
+// workspace rows are padded to 64 bf16 / 128 int8, whole 128-byte runs (the largest stage row)
+constexpr int BKB = kTileRowBytes;
 
 // A tile configuration: BM x BN tile, WM x WN waves, NSTAGE LDS buffers of SB bytes of K per
 // row (128: 64 bf16; 64: 32 bf16, twice the stages in the same LDS).

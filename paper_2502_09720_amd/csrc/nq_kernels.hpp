@@ -84,6 +84,15 @@ struct MatmulOperand {
 // every integer up to 256, fp16 up to 2048, int8 up to 127 (all exact).
 enum ElemType { ET_BF16 = 0, ET_F16 = 1, ET_I8 = 2 };
 
+// Whether every m X2 of an operand fits int8.  A decoded point lies in the closed cell
+// q V(2E8), |X2| <= 2q.  2q e_i and -2q e_i are the only points there with a coordinate of
+// size 2q (the cell's radius is 2q) and all 16 share one code word, which the full decoder's
+// tie rules send to -2q e_0; so its coordinates lie in [-2q, 2q - 1] and 2q m = 128 still
+// fits.  NestQuantM reaches +2q at coordinate 0.
+inline bool tiles_fit_i8(int q, int m_max, int decoder) {
+  return 2 * q * m_max <= (decoder == 0 ? 128 : 127);
+}
+
 hipError_t launch_encode(const void* x, int dtype, int64_t rows, int cols, int64_t ld_x,
                          const EncodeArgs& a, uint32_t* codes, uint32_t* beta, float* scales,
                          hipStream_t st);

@@ -296,30 +296,41 @@ static uint32_t max_mult(uint32_t t) {
   return std::max(std::max(t & 0xFFu, (t >> 8) & 0xFFu), std::max((t >> 16) & 0xFFu, t >> 24));
 }
 
+// Padded blocks per row of the integer-dot GEMV's activation (whole steps of 8 blocks).
+static int dot_blocks(int nb) { return (nb + 7) / 8 * 8; }
+
+// The integer-dot GEMV takes one or two activation rows (any element type: it reads no
+// tile) when their int8 X2 and multiples, 9 bytes a block, fit 48 KiB of LDS and a row's
+// exact sum fits 32 bits: |X2| <= 2q per coordinate, so |sum| <= blocks * 8 * (2 q_A)(2 q_W) *
+// max m_A * max m_W.
+static bool takes_dot(const MatmulOperand& A, const MatmulOperand& W, int nb) {
+  const int nbp = dot_blocks(nb);
+  return A.rows <= 2 && A.rows * nbp * 9 <= 49152 &&
+         (double)nbp * 8.0 * (2.0 * A.q) * (2.0 * W.q) * (double)max_mult(A.mtab) *
+                 (double)max_mult(W.mtab) < 2147483647.0;
+}
+
+static hipError_t dot_launch(const MatmulOperand& A, const MatmulOperand& W, int nb, float* c,
+                             int64_t ldc, float scale, hipStream_t st) {
+  const unsigned grid = (unsigned)((W.rows + 15) / 16);
+  const int nbp = dot_blocks(nb);
+  const size_t lds = (size_t)A.rows * nbp * 9;        // int8 X2 (8 bytes) + m_A per block
+#define NQ_SKD(DV)                                                                             \
+  hipLaunchKernelGGL((skinny_kernel<1, ET_BF16, DV, 8, true, true>), dim3(grid), dim3(512),    \
+                     lds, st, (const u32x4*)nullptr, nbp, A, W, nb, c, ldc, scale)
+  // NestQuantM (variants 1 and 2) on the byte decoder: cheaper than decode_word_m16 here,
+  // where the int8 form costs one XOR a word against three
+  if (decoder_variant(W.decoder, W.q) == 0) NQ_SKD(0); else NQ_SKD(1);
+#undef NQ_SKD
+  return hipGetLastError();
+}
+
 template <int ET>
 static hipError_t skinny_launch(const MatmulOperand& A, const MatmulOperand& W, const u32x4* ta,
                                 int kcb, int nb, float* c, int64_t ldc, float scale,
                                 bool adec, hipStream_t st) {
   const int64_t mp = (A.rows + 15) / 16 * 16;
   const unsigned grid = (unsigned)((W.rows + 15) / 16);
-  // the integer-dot GEMV when a row's exact sum fits 32 bits: |X2| <= 2q per coordinate, so
-  // |sum| <= nbp * 8 * (2 q_A)(2 q_W) * max m_A * max m_W
-  const int nbp = kcb * 16 / (ET == ET_I8 ? 8 : 16);
-  const bool dot = adec && ET != ET_I8 &&
-                   (double)nbp * 8.0 * (2.0 * A.q) * (2.0 * W.q) * (double)max_mult(A.mtab) *
-                           (double)max_mult(W.mtab) < 2147483647.0;
-  if (dot) {
-    const size_t lds = (size_t)A.rows * nbp * 9;      // int8 X2 (8 bytes) + m_A per block
-#define NQ_SKD(DV)                                                                           \
-  hipLaunchKernelGGL((skinny_kernel<1, ET, DV, 8, true, true>), dim3(grid), dim3(512), lds,  \
-                     st, ta, kcb, A, W, nb, c, ldc, scale)
-    // NestQuantM (variants 1 and 2) on the byte decoder: cheaper than decode_word_m16 here,
-    // where the int8 form costs one XOR a word against three
-    const int dv = decoder_variant(W.decoder, W.q);
-    if (dv == 0) NQ_SKD(0); else NQ_SKD(1);
-#undef NQ_SKD
-    return hipGetLastError();
-  }
   if (adec) {
     const size_t lds = (size_t)A.rows * kcb * 16;
 #define NQ_SKA(DV)                                                                             \
@@ -359,8 +370,9 @@ static hipError_t skinny(int stages, const MatmulOperand& A, const MatmulOperand
   u32x4* ta = reinterpret_cast<u32x4*>(ws);
   // one or two activation rows whose tile fits 48 KiB of LDS: the product kernel decodes
   // them itself (no decode stage of its own)
-  const bool adec = A.rows <= 2 && A.rows * (int64_t)kcb * 16 <= 49152;
-  if ((stages & 1) && !adec) launch_tiles<ET>(A, nb, mp, nbp, (void*)ta, st);
+  const bool dot = takes_dot(A, W, nb);
+  const bool adec = !dot && A.rows <= 2 && A.rows * (int64_t)kcb * 16 <= 49152;
+  if ((stages & 1) && !adec && !dot) launch_tiles<ET>(A, nb, mp, nbp, (void*)ta, st);
   if (!(stages & 2)) return hipGetLastError();
   // W in column ranges whose code words stay below 2^31 bytes (buffer-load offsets)
   const int64_t max_rows = (((int64_t)1 << 31) - 1) / ((int64_t)nb * 4) / 16 * 16;
@@ -371,7 +383,8 @@ static hipError_t skinny(int stages, const MatmulOperand& A, const MatmulOperand
     Wc.beta = W.beta + r0 * ((nb + 15) / 16);
     Wc.scales = W.scales + r0;
     Wc.rows = rows;
-    const hipError_t e = skinny_launch<ET>(A, Wc, ta, kcb, nb, c + r0, ldc, scale, adec, st);
+    const hipError_t e = dot ? dot_launch(A, Wc, nb, c + r0, ldc, scale, st)
+                             : skinny_launch<ET>(A, Wc, ta, kcb, nb, c + r0, ldc, scale, adec, st);
     if (e != hipSuccess) return e;
   }
   return hipGetLastError();
