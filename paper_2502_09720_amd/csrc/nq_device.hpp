@@ -135,15 +135,24 @@ __device__ __forceinline__ void nearest_e8(const float (&y)[8], int (&P)[8]) {
   e8_point(k, d8, P);
 }
 
-// nearest_e8 without the exact fallback: false (P unset) when the fp32 gap cannot decide.
-__device__ __forceinline__ bool nearest_e8_fast(const float (&y)[8], int (&P)[8]) {
-  E8Cand k;
-  e8_candidates(y, k);
-  if (fabsf(k.gap) < 1.0e-5f) return false;
-  e8_point(k, k.gap < 0.0f, P);
-  return true;
+// max and min of three absolute values in one instruction; written out because fmaxf of a
+// value that may be a signalling NaN (bits of a loaded word) costs a canonicalisation first.
+__device__ __forceinline__ float max3_abs(float a, float b, float c) {
+  float r;
+  asm("v_max3_f32 %0, |%1|, |%2|, |%3|" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
 }
-
+__device__ __forceinline__ float min3_abs(float a, float b, float c) {
+  float r;
+  asm("v_min3_f32 %0, |%1|, |%2|, |%3|" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
+}
+// The median of m1, m2 and |a|.
+__device__ __forceinline__ float med3_abs(float m1, float m2, float a) {
+  float r;
+  asm("v_med3_f32 %0, %1, %2, |%3|" : "=v"(r) : "v"(m1), "v"(m2), "v"(a));
+  return r;
+}
 // max over the 240 roots lambda of E8 of <P, lambda> for P in 2E8 units:
 // max( |P|_(1) + |P|_(2),  (sum |P_i| - 2 [odd number of negative P_i] min |P_i|) / 2 ).
 // P lies strictly inside the cell q V of q 2E8 iff the bound is < 2q, strictly outside iff
@@ -174,22 +183,21 @@ __device__ __forceinline__ int e8_root_bound(const int (&P)[8]) {
 // nearest point p of E8 to x, |max<2p, lambda> - 2 max<x, lambda>| <= 2 |p - x| |lambda|
 // <= 2 sqrt(2), since the covering radius of E8 is 1 and roots have norm sqrt(2).
 __device__ __forceinline__ float root_bound_f(const float (&x)[8]) {
-  float a[8];
-#pragma unroll
-  for (int l = 0; l < 8; ++l) a[l] = fabsf(x[l]);
-  float m1 = fmaxf(a[0], a[1]), m2 = fminf(a[0], a[1]);
+  float m1 = max3_abs(x[0], x[1], x[1]), m2 = min3_abs(x[0], x[1], x[1]);
+  uint32_t sx = __float_as_uint(x[0]) ^ __float_as_uint(x[1]);
+  float sa = fabsf(x[0]) + fabsf(x[1]);
 #pragma unroll
   for (int l = 2; l < 8; ++l) {
-    m2 = fmaxf(m2, fminf(m1, a[l]));
-    m1 = fmaxf(m1, a[l]);
+    m2 = med3_abs(m1, m2, x[l]);   // the second largest: m2 <= m1
+    m1 = max3_abs(m1, x[l], x[l]);
+    sa = sa + fabsf(x[l]);
+    sx ^= __float_as_uint(x[l]);
   }
-  const float sa = ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
-  const float mn = fminf(fminf(fminf(a[0], a[1]), fminf(a[2], a[3])),
-                         fminf(fminf(a[4], a[5]), fminf(a[6], a[7])));
-  int neg = 0;
-#pragma unroll
-  for (int l = 0; l < 8; ++l) neg ^= (x[l] < 0.0f) ? 1 : 0;
-  return fmaxf(m1 + m2, 0.5f * (sa - (neg ? 2.0f * mn : 0.0f)));
+  const float mn = min3_abs(min3_abs(x[0], x[1], x[2]), min3_abs(x[3], x[4], x[5]),
+                            min3_abs(x[6], x[7], x[7]));
+  // sx's sign: an odd number of negative entries (a -0 makes mn 0, so its sign is no matter)
+  const float fix = __uint_as_float(__float_as_uint(mn) & (uint32_t)((int)sx >> 31));
+  return fmaxf(m1 + m2, __builtin_fmaf(0.5f, sa, -fix));
 }
 
 // v mod q in [0, q): exact for |v| < 2^24 (fp32 reciprocal estimate and one correction).
@@ -298,6 +306,13 @@ typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 
 #include "nq_b8.hpp"
 
+// Dot product of four signed bytes, plus acc.
+__device__ __forceinline__ int dot4_i8(uint32_t a, uint32_t b, int acc) {
+  return __builtin_amdgcn_sdot4((int)a, (int)b, acc, false);
+}
+
+#include "nq_e8b.hpp"
+
 // ---------------------------------------------------------------------------------------
 // NestQuantM decode at q = 16 with four coordinates per register (byte SIMD).  With 2q = 32
 // every X = G c fits a byte (X4 <= 15 + 2 * 120 = 255, the others <= 45), floor(X / 32) and
@@ -387,6 +402,17 @@ __device__ __forceinline__ uint32_t pack16(float lo, float hi) {
   }
 }
 
+// m * X2 as eight 16-bit values from the bytes X2 + 128: m (byte - 128) is one exact fma.
+template <bool F16>
+__device__ __forceinline__ u32x4 tile_16_from_b8(uint32_t xa, uint32_t xb, int m) {
+  const float fm = (float)m, off = -128.0f * fm;
+  auto val = [&](uint32_t x, int b) {
+    return __builtin_fmaf((float)((x >> (8 * b)) & 0xFFu), fm, off);
+  };
+  return u32x4{pack16<F16>(val(xa, 0), val(xa, 1)), pack16<F16>(val(xa, 2), val(xa, 3)),
+               pack16<F16>(val(xb, 0), val(xb, 1)), pack16<F16>(val(xb, 2), val(xb, 3))};
+}
+
 // m * X2 of one block as eight bf16 or fp16 values, coordinates 2i and 2i+1 in word i.
 // |X2| <= 2q <= 32, so the values are exact integers in bf16 while |m X2| <= 256 (m <= 4
 // for every q, the uniform beta grid) and in fp16 while |m X2| <= 2048 (m <= 64).  DV 0 and 1
@@ -409,12 +435,7 @@ __device__ __forceinline__ u32x4 decode_tile_16(uint32_t w, int m, int q, uint32
   }
   uint32_t xa, xb;
   decode_word_b8<DV == 1>(w, q, m2q, xa, xb);
-  const float fm = (float)m, off = -128.0f * fm;
-  auto val = [&](uint32_t x, int b) {
-    return __builtin_fmaf((float)((x >> (8 * b)) & 0xFFu), fm, off);   // m (byte - 128), exact
-  };
-  return u32x4{pack16<F16>(val(xa, 0), val(xa, 1)), pack16<F16>(val(xa, 2), val(xa, 3)),
-               pack16<F16>(val(xb, 0), val(xb, 1)), pack16<F16>(val(xb, 2), val(xb, 3))};
+  return tile_16_from_b8<F16>(xa, xb, m);
 }
 
 // m * X2 of one block as eight int8 (exact when m X2 fits, see tiles_fit_i8), the coordinates
@@ -422,10 +443,7 @@ __device__ __forceinline__ u32x4 decode_tile_16(uint32_t w, int m, int q, uint32
 // apart): the low byte of a product depends on the low bytes of its factors alone, so the
 // other byte of a lane needs no mask, and one v_perm gathers the four low bytes.
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-template <int DV = 0>
-__device__ __forceinline__ u32x2 decode_tile_i8(uint32_t w, int m, int q, uint32_t m2q) {
-  uint32_t xa, xb;
-  decode_word_b8<DV != 0>(w, q, m2q, xa, xb);
+__device__ __forceinline__ u32x2 tile_i8_from_b8(uint32_t xa, uint32_t xb, int m) {
   const uint32_t mm = (uint32_t)m | ((uint32_t)m << 16);   // m in both halves
   auto mul8 = [&](uint32_t x) {
     const uint32_t s = x ^ 0x80808080u;                  // X2 as signed bytes
@@ -434,6 +452,12 @@ __device__ __forceinline__ u32x2 decode_tile_i8(uint32_t w, int m, int q, uint32
     return __builtin_amdgcn_perm(hi, lo, 0x06020400u);
   };
   return u32x2{mul8(xa), mul8(xb)};
+}
+template <int DV = 0>
+__device__ __forceinline__ u32x2 decode_tile_i8(uint32_t w, int m, int q, uint32_t m2q) {
+  uint32_t xa, xb;
+  decode_word_b8<DV != 0>(w, q, m2q, xa, xb);
+  return tile_i8_from_b8(xa, xb, m);
 }
 
 // X2 of one block as eight int8 (|X2| <= 2q <= 32), the coordinates in byte order, with no

@@ -62,13 +62,39 @@ __device__ __forceinline__ void load_block<_Float16>(const _Float16* __restrict_
   }
 }
 
+// v of the lane whose index differs in the bits of M (1, 2), or of the mirrored lane of the
+// half row or row (M = 4, 8): once the lanes of each aligned group of M hold one value, the
+// mirrored lane holds that of lane ^ M.  One DPP move, where a general shuffle goes through LDS.
+template <int M>
+__device__ __forceinline__ uint32_t dpp_across(uint32_t v) {
+  constexpr int ctrl = M == 1 ? 0xB1 : (M == 2 ? 0x4E : (M == 4 ? 0x141 : 0x140));
+  return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, ctrl, 0xF, 0xF, true);
+}
+template <int M>
+__device__ __forceinline__ double dpp_add(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint64_t o = (uint64_t)dpp_across<M>((uint32_t)u) |
+                     (uint64_t)dpp_across<M>((uint32_t)(u >> 32)) << 32;
+  return v + __builtin_bit_cast(double, o);
+}
+// Sum over aligned groups of LANES lanes of a wave (8 to 64), the same in each of its lanes.
+template <int LANES>
+__device__ __forceinline__ double wave_sum(double v) {
+  v = dpp_add<1>(v);
+  v = dpp_add<2>(v);
+  v = dpp_add<4>(v);
+  if constexpr (LANES > 8) v = dpp_add<8>(v);
+#pragma unroll
+  for (int m = 16; m < LANES; m <<= 1) v += __shfl_xor(v, m, 64);
+  return v;
+}
+
 // Sum over the LANES lanes of a row group.  LANES <= 64: within the wave by xor shuffles
 // (every lane ends with the same, bit-identical sum).  LANES > 64: the workgroup is exactly
 // one row (LANES threads); wave sums are combined through LDS in a fixed order.
 template <int LANES>
 __device__ __forceinline__ double group_sum(double v, double* red) {
-#pragma unroll
-  for (int m = 1; m < (LANES < 64 ? LANES : 64); m <<= 1) v += __shfl_xor(v, m, 64);
+  v = wave_sum<(LANES < 64 ? LANES : 64)>(v);
   if constexpr (LANES > 64) {
     const int wave = threadIdx.x >> 6;
     __syncthreads();
@@ -141,10 +167,8 @@ __device__ __forceinline__ float next_down(float v) { return __uint_as_float(__f
 // statistic s = max(2 max_{i>0} |x_i|, |x_0|) has s c > (q + 2)(1 + 2^-12) surely overloads
 // at the multiplier c (the slack covers the rounding of y = fl32(x c)).
 __device__ __forceinline__ float m_stat(const float (&x)[8]) {
-  float m = fabsf(x[1]);
-#pragma unroll
-  for (int l = 2; l < 8; ++l) m = fmaxf(m, fabsf(x[l]));
-  return fmaxf(2.0f * m, fabsf(x[0]));
+  const float m = max3_abs(max3_abs(x[1], x[2], x[3]), max3_abs(x[4], x[5], x[6]), x[7]);
+  return max3_abs(2.0f * m, x[0], x[0]);
 }
 __device__ __forceinline__ bool m_skip(float s, float c, int q) {
   return s * c > (float)(q + 2) * (1.0f + 0x1p-12f);
@@ -237,6 +261,21 @@ __device__ __forceinline__ void tile_from_x2(const EncodeArgs& a, int64_t row, i
       o[i] = a.tile_et == ET_F16 ? pack16<true>(lo, hi) : pack16<false>(lo, hi);
     }
     reinterpret_cast<u32x4*>(a.tiles)[idx] = u32x4{o[0], o[1], o[2], o[3]};
+  }
+}
+
+// The same for a point in bytes (P_l + 64 in 0..127).
+__device__ __forceinline__ void tile_from_bytes(const EncodeArgs& a, int64_t row, int j,
+                                                const E8Bytes& P, int t) {
+  const int m = (int)((a.mtab >> (8 * t)) & 0xFFu);
+  const int64_t idx = row * a.nb_p + j;
+  const uint32_t xa = P.a + 0x40404040u, xb = P.b + 0x40404040u;   // P_l + 128
+  if (a.tile_et == ET_I8) {
+    reinterpret_cast<u32x2*>(a.tiles)[idx] = tile_i8_from_b8(xa, xb, m);
+  } else if (a.tile_et == ET_F16) {
+    reinterpret_cast<u32x4*>(a.tiles)[idx] = tile_16_from_b8<true>(xa, xb, m);
+  } else {
+    reinterpret_cast<u32x4*>(a.tiles)[idx] = tile_16_from_b8<false>(xa, xb, m);
   }
 }
 
@@ -523,11 +562,40 @@ struct SlotMap {
   }
 };
 
-// One evaluation of a queued block at beta t: its exact nearest point P, and whether the
-// search stops there (the last beta, or a point that does not overload).  The root bound of
-// x is not consulted: the integer root bound of P settles every point off the cell
-// boundary, and a point it cannot settle is decided by the literal test.
-__device__ __forceinline__ bool eval_block(const float (&v)[8], float ct, int t,
+// What one evaluation of a block at a beta says.
+enum Verdict {
+  KEEP,       // the point is reproduced: coded here
+  NEXT,       // it overloads and there is a larger beta
+  BOUNDARY,   // on the cell boundary (full decoder, t < k - 1): the literal test decides
+  EXACT       // not for the byte form: too close to call in fp32, or at the last beta and not
+              // strictly inside the cell
+};
+
+// Block v at beta t in the byte form: the point P and, when it is kept, its code word.  The
+// root bound of P settles every point off the cell boundary; NestQuantM has no such bound,
+// so there the word is decoded again.  |v| ct must be within kE8BytesMax.
+__device__ __forceinline__ Verdict eval_bytes(const float (&v)[8], float ct, int t,
+                                              const EncodeArgs& a, E8Bytes& P, uint32_t& word) {
+  if (!nearest_e8_bytes(v, ct, P)) return EXACT;
+  const bool last = t == a.k - 1;
+  if (a.decoder) {
+    // outside the decoder's box the word means nothing, and its decode, which lies inside
+    // the box, differs from P
+    word = encode_e8_bytes<true>(P, a.q, a.mq);
+    uint32_t xa, xb;
+    decode_word_b8<true>(word, a.q, a.m2q, xa, xb);
+    const bool same = xa == P.a + 0x40404040u && xb == P.b + 0x40404040u;
+    return same ? KEEP : (last ? EXACT : NEXT);
+  }
+  const int M = e8_bytes_root_bound(P);
+  word = encode_e8_bytes(P, a.q, a.mq);
+  if (M < 2 * a.q) return KEEP;
+  return last ? EXACT : (M > 2 * a.q ? NEXT : BOUNDARY);
+}
+
+// One evaluation of a queued block at beta t in the exact arithmetic: its nearest point P, and
+// whether the search stops there (the last beta, or a point that does not overload).
+__device__ __forceinline__ bool eval_exact(const float (&v)[8], float ct, int t,
                                            const EncodeArgs& a, int (&P)[8]) {
   float y[8];
 #pragma unroll
@@ -635,7 +703,7 @@ __attribute__((amdgpu_waves_per_eu(LANES >= 128 || (LANES == 64 && BPT == 1) ? 5
   __shared__ uint16_t qnext[NW * SLOTS];
   __shared__ int qcnt[4];
   __shared__ uint16_t bq[BQ];                      // boundary slots: w << 11 | sl << 2 | t
-  __shared__ uint2 bp[BQ];                         // and their points, as signed bytes
+  __shared__ uint2 bp[BQ];                         // and their points, as bytes P_l + 64
   __shared__ int bcnt;
   __shared__ uint8_t tsl[NW][SLOTS];
   __shared__ float crow[CW][RW][4];
@@ -716,8 +784,7 @@ __attribute__((amdgpu_waves_per_eu(LANES >= 128 || (LANES == 64 && BPT == 1) ? 5
         part += s;
       }
     }
-#pragma unroll
-    for (int m = 1; m < 64; m <<= 1) part += __shfl_xor(part, m, 64);
+    part = wave_sum<64>(part);
     if (lane == 0) rsum[wave][0] = part;
   } else {
     RawBlock<T> raw[BPT];
@@ -743,30 +810,28 @@ __attribute__((amdgpu_waves_per_eu(LANES >= 128 || (LANES == 64 && BPT == 1) ? 5
 #pragma unroll
       for (int l = 0; l < 8; ++l) s = __builtin_fma((double)v[l], (double)v[l], s);
       if constexpr (LANES < 64) {
-#pragma unroll
-        for (int m = 1; m < LANES; m <<= 1) s += __shfl_xor(s, m, 64);
+        s = wave_sum<LANES>(s);
         if (lane % LANES == 0) rsum[wave][SM::row_w(i, lane)] = s;
       } else {
         part += s;
       }
     }
     if constexpr (LANES >= 64) {
-#pragma unroll
-      for (int m = 1; m < 64; m <<= 1) part += __shfl_xor(part, m, 64);
+      part = wave_sum<64>(part);
       if (lane == 0) rsum[wave][0] = part;
     }
   }
   __syncthreads();
 
   // ---- row scales and multipliers ----
-  // One lane per row; with one row per workgroup, lanes 0-3 of wave 0 all find the scale
-  // (the same instructions) and then each the multiplier and threshold of its own beta.
-  {
-    constexpr int TL = SM::WGROW ? 4 : 1;   // lanes per row
-    const bool mine = SM::WGROW ? threadIdx.x < TL : lane < RW;
-    const int rw = SM::WGROW ? 0 : lane;
+  // Four lanes per row, one per beta: all four find the scale (the same instructions) and
+  // then each the multiplier and threshold of its own beta (one double division a lane
+  // where a lane per row took four, with most of the wave idle).  One row per workgroup:
+  // wave 0 alone; the other rows: each wave its own, 16 at a time.
+  for (int e = lane; e < 4 * RW && (!SM::WGROW || wave == 0); e += 64) {
+    const int rw = e >> 2, t = e & 3;
     const int64_t row = row0 + rw;
-    if (mine && row < rows) {
+    if (row < rows) {
       double s = rsum[wave][rw];
       if constexpr (SM::WGROW) {
         s = rsum[0][0];
@@ -786,25 +851,21 @@ __attribute__((amdgpu_waves_per_eu(LANES >= 128 || (LANES == 64 && BPT == 1) ? 5
 #pragma unroll
           for (int l = 0; l < 8; ++l) dd_add_square(hi, lo, v[l]);
         }
-        double t, e;
-        two_sum(hi, lo, t, e);
-        r = exact_rms(t, e, n, r);
+        double sd, ed;
+        two_sum(hi, lo, sd, ed);
+        r = exact_rms(sd, ed, n, r);
       }
       const bool coded = (r > 0.0f) && isfinite(r);
-      auto set_beta = [&](int t) {
-        const double rb = (double)r * a.beta[t];
-        crow[cw][rw][t] = coded ? (float)(1.0 / rb) : 0.0f;
-        chi[cw][rw][t] = (coded && t < a.k - 1)
-                             ? (a.decoder ? skip_threshold_m(rb, a.q) : skip_threshold(rb, a.q))
-                             : INFINITY;
-      };
-      if constexpr (SM::WGROW) {
-        set_beta((int)threadIdx.x);
-      } else {
-#pragma unroll
-        for (int t = 0; t < 4; ++t) set_beta(t);
-      }
-      if (SM::WGROW ? threadIdx.x == 0 : true) {
+      const double rb = (double)r * a.beta[t];
+      crow[cw][rw][t] = coded ? (float)(1.0 / rb) : 0.0f;
+      // betas 0..2: the threshold above which a block surely overloads there and starts at a
+      // later one (infinite from the last beta on).  Entry 3: the largest |x| the byte form
+      // takes at the last beta; at the others the thresholds keep |y| below q + 3.
+      float hi = INFINITY;
+      if (coded && t < 3 && t < a.k - 1) hi = a.decoder ? skip_threshold_m(rb, a.q) : skip_threshold(rb, a.q);
+      if (t == 3) hi = (float)((double)kE8BytesMax * (1.0 - 0x1p-16) * ((double)r * a.beta[a.k - 1]));
+      chi[cw][rw][t] = hi;
+      if (t == 0) {
         rrow[cw][rw] = coded ? r : 0.0f;
         scales[row] = r;
       }
@@ -823,8 +884,9 @@ __attribute__((amdgpu_waves_per_eu(LANES >= 128 || (LANES == 64 && BPT == 1) ? 5
     const bool valid = row < rows && j < nb;
     const bool coded = valid && rrow[cw][rw] != 0.0f;
     bool queued = false, bnd = false;
-    int start = 0, t0 = 0, amax = 0;
-    int P[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    int start = 0, t0 = 0;
+    uint32_t word = 0u;
+    E8Bytes P{0x40404040u, 0x40404040u};
     if (coded) {
       float v[8];
       slot_block(wave, sl, v);
@@ -832,35 +894,11 @@ __attribute__((amdgpu_waves_per_eu(LANES >= 128 || (LANES == 64 && BPT == 1) ? 5
       const float mx = a.decoder ? m_stat(v) : root_bound_f(v);
       const f32x4 hi = *reinterpret_cast<const f32x4*>(chi[cw][rw]);
       t0 = mx > hi.x ? (mx > hi.y ? (mx > hi.z ? 3 : 2) : 1) : 0;
-      const float ct = crow[cw][rw][t0];
-      float y[8];
-#pragma unroll
-      for (int l = 0; l < 8; ++l) y[l] = v[l] * ct;
-      if (!nearest_e8_fast(y, P)) {
-        queued = true;                 // decision too close for fp32: redo exactly
-        start = t0;
-      } else if (a.decoder) {
-        amax = 1 << 30;                // not known: encode_codes finds it
-        if (t0 < a.k - 1 && overloaded_m(P, a.q, a.mq, a.m2q)) {   // its decoder decides
-          queued = true;
-          start = t0 + 1;
-        }
-      } else {
-        const int M = e8_root_bound(P, amax);
-        if (t0 < a.k - 1) {
-          if (M > 2 * a.q) {           // overloads: the next beta, later
-            queued = true;
-            start = t0 + 1;
-          } else if (M == 2 * a.q) {   // on the boundary: the literal test decides, later
-            bnd = true;
-          }
-        } else if (TILES && M >= 2 * a.q) {
-          // the last beta, where a point may overload: only a point strictly inside the
-          // cell is its own decode; the others take the decoder's tile in phase 2
-          queued = true;
-          start = t0;
-        }
-      }
+      const Verdict vd = eval_bytes(v, crow[cw][rw][t0], t0, a, P, word);
+      // mx bounds every |x_l|: past hi.w the bytes may have wrapped
+      queued = vd == NEXT || vd == EXACT || mx > hi.w;
+      bnd = vd == BOUNDARY && !queued;
+      start = t0 + (vd == NEXT && !(mx > hi.w) ? 1 : 0);
     }
     // boundary points go to the boundary list with P (|P_l| <= 2q), while it has room, and
     // to the queue at the same beta otherwise
@@ -876,12 +914,7 @@ __attribute__((amdgpu_waves_per_eu(LANES >= 128 || (LANES == 64 && BPT == 1) ? 5
         if (bi < BQ) {
           listed = true;
           bq[bi] = (uint16_t)((wave << 11) | (sl << 2) | t0);
-          // low bytes of P_0..P_3 and P_4..P_7 (byte selects 0 and 4 of each pair; 12 = zero)
-          auto pack4 = [](int p0, int p1, int p2, int p3) {
-            return __builtin_amdgcn_perm((uint32_t)p1, (uint32_t)p0, 0x0C0C0400u) |
-                   __builtin_amdgcn_perm((uint32_t)p3, (uint32_t)p2, 0x04000C0Cu);
-          };
-          bp[bi] = uint2{pack4(P[0], P[1], P[2], P[3]), pack4(P[4], P[5], P[6], P[7])};
+          bp[bi] = uint2{P.a, P.b};
         } else {
           queued = true;
           start = t0;
@@ -893,23 +926,10 @@ __attribute__((amdgpu_waves_per_eu(LANES >= 128 || (LANES == 64 && BPT == 1) ? 5
       const int pos = qn + __popcll(mask & lanes_below);
       queue[wave][pos] = (uint16_t)((sl << 2) | start);
     } else if (valid && !listed) {
-      uint32_t word = 0u;
-      if (coded) {
-        word = amax < (1 << 30) ? encode_codes_amax(P, a.q, a.rq, a.mq, amax)
-                                : encode_codes(P, a.q, a.rq, a.mq);
-      }
       codes_w[__mul24(rw, nb) + j] = word;   // rw = 0 or nb <= 64
       tsl[wave][sl] = (uint8_t)t0;
-      if constexpr (TILES) {
-        // a point kept here passed the overload test or lies strictly inside the cell, so
-        // X2 = P (zero for rows that are not coded); the NestQuantM decoder has no such
-        // bound at the last beta, where its tile is decoded
-        if (coded && a.decoder && t0 == a.k - 1) {
-          tile_decoded(a, row, j, word, t0);
-        } else {
-          tile_from_x2(a, row, j, P, t0);
-        }
-      }
+      // a point kept here is its own decode, X2 = P (zero for rows that are not coded)
+      if constexpr (TILES) tile_from_bytes(a, row, j, P, t0);
     }
     qn += __popcll(mask);
   }
@@ -929,8 +949,8 @@ __attribute__((amdgpu_waves_per_eu(LANES >= 128 || (LANES == 64 && BPT == 1) ? 5
         int P[8];
 #pragma unroll
         for (int l = 0; l < 4; ++l) {
-          P[l] = (int)(int8_t)(uint8_t)(pb.x >> (8 * l));
-          P[4 + l] = (int)(int8_t)(uint8_t)(pb.y >> (8 * l));
+          P[l] = (int)((pb.x >> (8 * l)) & 0xFFu) - 64;
+          P[4 + l] = (int)((pb.y >> (8 * l)) & 0xFFu) - 64;
         }
         if (!boundary_overloaded(P, a.q, a.mq, a.m2q)) {
           const int i = sl >> 6, l = sl & 63;
@@ -996,20 +1016,35 @@ __attribute__((amdgpu_waves_per_eu(LANES >= 128 || (LANES == 64 && BPT == 1) ? 5
           const int c2 = SM::WGROW ? 0 : w;
           float v[8];
           slot_block(w, sl, v);
-          int P[8];
-          if (eval_block(v, crow[c2][rw][t], t, a, P)) {
-            const uint32_t word = encode_codes(P, a.q, a.rq, a.mq);
+          const float ct = crow[c2][rw][t];
+          const float vmax = max3_abs(max3_abs(v[0], v[1], v[2]), max3_abs(v[3], v[4], v[5]),
+                                      max3_abs(v[6], v[7], v[7]));
+          E8Bytes Pb;
+          uint32_t word;
+          const Verdict vd = vmax <= chi[c2][rw][3] ? eval_bytes(v, ct, t, a, Pb, word) : EXACT;
+          if (vd == KEEP) {
             codes[code_at(w, rw, j)] = word;
             tsl[w][sl] = (uint8_t)t;
-            if constexpr (TILES) {
-              if (t < a.k - 1) {
-                tile_from_x2(a, row, j, P, t);
+            if constexpr (TILES) tile_from_bytes(a, row, j, Pb, t);
+          } else {
+            more = vd == NEXT;
+            if (!more) {
+              int P[8];
+              if (eval_exact(v, ct, t, a, P)) {
+                word = encode_codes(P, a.q, a.rq, a.mq);
+                codes[code_at(w, rw, j)] = word;
+                tsl[w][sl] = (uint8_t)t;
+                if constexpr (TILES) {
+                  if (t < a.k - 1) {
+                    tile_from_x2(a, row, j, P, t);
+                  } else {
+                    tile_decoded(a, row, j, word, t);
+                  }
+                }
               } else {
-                tile_decoded(a, row, j, word, t);
+                more = true;
               }
             }
-          } else {
-            more = true;
             next = ((uint32_t)w << 11) | ((uint32_t)sl << 2) | (uint32_t)(t + 1);
           }
         }
@@ -1039,8 +1074,10 @@ __attribute__((amdgpu_waves_per_eu(LANES >= 128 || (LANES == 64 && BPT == 1) ? 5
     const int64_t row = row0 + rw;
     const bool ok = row < rows && j < nb;
     uint32_t bits = ok ? (uint32_t)tsl[wave][i * 64 + lane] << (2 * (j & 15)) : 0u;
-#pragma unroll
-    for (int m = 1; m < G; m <<= 1) bits |= (uint32_t)__shfl_xor((int)bits, m, 64);
+    bits |= dpp_across<1>(bits);
+    bits |= dpp_across<2>(bits);
+    bits |= dpp_across<4>(bits);
+    if constexpr (G > 8) bits |= dpp_across<8>(bits);
     if (ok && (j & 15) == 0) beta_w[__mul24(rw, nbw) + (j >> 4)] = bits;   // rw = 0 or nbw <= 4
   }
 }
