@@ -375,8 +375,21 @@ __device__ __forceinline__ float exact_rms(double hi, double lo, double n, float
 // The fp32 RMS candidate from an fp64 sum, and whether it is certainly RN32(sqrt(S / n)):
 // the fp64 sum has relative error below 2^-46 here, so S farther than 2^-40 S from both
 // rounding-boundary squares n m^2 settles the rounding.
-__device__ __forceinline__ float rms_candidate(double s, double n, bool& sure) {
-  const float r = (float)__builtin_sqrt(s / n);
+//
+// The candidate itself need not be rounded right (sure says whether it is), so the mean is a
+// product with 1 / n and its root two steps from the hardware's reciprocal root, in place of
+// an IEEE division and square root (about 40 vector instructions).
+__device__ __forceinline__ float rms_candidate(double s, double n, double inv_n, bool& sure) {
+  const double q = s * inv_n;
+  float r;
+  if (q > 0.0 && q < INFINITY) {
+    const double y = __builtin_amdgcn_rsq(q), h = 0.5 * y;
+    double g = q * y;
+    g = __builtin_fma(g, __builtin_fma(-h, g, 0.5), g);
+    r = (float)__builtin_fma(__builtin_fma(-g, g, q), h, g);
+  } else {
+    r = (float)__builtin_sqrt(q);
+  }
   sure = true;
   if (s > 0.0 && r > 0.0f && isfinite(r)) {
     const double m_hi = 0.5 * ((double)r + (double)next_up(r));
@@ -442,7 +455,7 @@ __global__ __launch_bounds__(LANES > 64 ? LANES : 256) void encode_kernel(
 
   const double n = (double)cols;
   bool sure;
-  float r = rms_candidate(s, n, sure);
+  float r = rms_candidate(s, n, 1.0 / n, sure);
   // With LANES > 64 there is one row per workgroup and every thread holds the same s, so
   // this branch (which synchronizes the workgroup) is uniform.
   if (!sure) {
@@ -511,32 +524,37 @@ __global__ __launch_bounds__(LANES > 64 ? LANES : 256) void encode_kernel(
 // ---------------------------------------------------------------------------------------
 // Slot-compacted encoder (rows of up to 2048 blocks).
 //
-// A workgroup of four waves (two with LANES = 128) owns 64 * BPT blocks per wave ("slots"):
-// slot s = 64 i + l of wave w is
-// block j of row row_w, with
+// A workgroup owns 64 * BPT blocks per wave ("slots"): slot s = 64 i + l of wave w is block j of
+// row row_w, with
 //   LANES <  64: row_w = i * (64 / LANES) + l / LANES, j = l % LANES  (a row per lane group
-//                and pass; 64 / LANES * BPT rows per wave)
-//   LANES == 64: row_w = 0, j = l + 64 i                              (one row per wave)
+//                and pass; 64 / LANES * BPT rows per wave; workgroups of one wave)
+//   LANES == 64: row_w = 0, j = l + 64 i                              (one row per wave, four
+//                waves)
 //   LANES >  64: row_w = 0, j = 64 w + l + LANES i                   (one row per workgroup
 //                of LANES / 64 waves)
-// Phase 0 reads every slot from HBM once (all of a lane's loads in flight together), stages
-// it in LDS and forms the row sums of squares; then one lane per row (one per beta, with one
-// row per workgroup) turns its sum into the scale r, the multipliers c_t and the thresholds
-// of skip_threshold.  Phase 1 evaluates every slot at the first beta the root bound of x
-// does not rule out, with the fp32 nearest-point decision, and finishes it unless that
-// decision was too close to call or the point's exact root bound says it overloads (both
-// queued, at the same and at the next beta), or the point lies on the cell boundary (kept
-// with its point in a boundary list).  Phase 2a runs the literal test on the boundary list;
-// phase 2 then finishes the queued slots (8.6% of the blocks on heavy-tailed Student-t rows,
-// fewer on Gaussian ones, plus the boundary points that overload) in rounds of one beta
-// each, the slots still searching compacted after every round so that the lanes stay busy.
-// With tiles, slots at the last beta whose point is not strictly inside the cell are queued
-// too, so that phase 1 never runs the decoder (full decoder only).
+// Phase 0 reads every slot from HBM (several of a lane's loads in flight together), stages it
+// in LDS (one-wave workgroups read it again instead) and forms the row sums of squares; then
+// a lane per row and beta turns the sum into the scale r, the multipliers c_t and the
+// thresholds of skip_threshold.  Phase 1 evaluates every slot, in the byte form, at the first
+// beta the root bound of x does not rule out, and finishes it when its point is strictly
+// inside the cell (full decoder) or reproduced (NestQuantM).  The others are queued: points
+// that overload at the next beta, points on the cell boundary, at the last beta outside the
+// cell, or too close to call in fp32 at the same one.  Phase 2 finishes the queue (11% of the
+// blocks of Gaussian rows) in rounds of one beta each, the slots still searching compacted
+// after every round so that the lanes stay busy; it takes the literal test on the boundary
+// and the exact path where the byte form declines.
 // Two-bit beta indices are staged in LDS and packed into words at the end.
+//
+// What bounds it: vector instructions, 1.09 per CU clock at 2^21 x 128 fp16 (382 us; 477 per
+// wave of 64 blocks, of which phase 1 takes 300; a build of 644 took 507 us).  There, one-wave
+// workgroups meet no barrier (462 -> 406 us: four waves waited while one finished the
+// workgroup's queue, a third of the time), unstaged blocks leave LDS for twice the waves, and
+// 12 passes a wave fill phase 2's lanes (398 us at 8, 382 at 12, 384 at 16).
 // ---------------------------------------------------------------------------------------
 template <int LANES, int BPT>
 struct SlotMap {
   static constexpr bool WGROW = LANES > 64;
+  static constexpr int NW = LANES > 64 ? LANES / 64 : (LANES < 64 ? 1 : 4);   // waves
   static constexpr int RPP = LANES < 64 ? 64 / LANES : 1;           // rows per pass
   static constexpr int ROWS_PER_WAVE = LANES < 64 ? RPP * BPT : 1;
   static constexpr int SLOTS = 64 * BPT;
@@ -566,31 +584,41 @@ struct SlotMap {
 enum Verdict {
   KEEP,       // the point is reproduced: coded here
   NEXT,       // it overloads and there is a larger beta
-  BOUNDARY,   // on the cell boundary (full decoder, t < k - 1): the literal test decides
-  EXACT       // not for the byte form: too close to call in fp32, or at the last beta and not
-              // strictly inside the cell
+  BOUNDARY,   // on the cell boundary (full decoder): the literal test decides
+  EXACT       // not for the byte form: too close to call in fp32, or a point at the last beta
+              // that may overload (strictly outside the cell; NestQuantM: not reproduced)
 };
 
-// Block v at beta t in the byte form: the point P and, when it is kept, its code word.  The
-// root bound of P settles every point off the cell boundary; NestQuantM has no such bound,
-// so there the word is decoded again.  |v| ct must be within kE8BytesMax.
+// Block v at beta t in the byte form: the point X it decodes to and, when it is kept, its code
+// word.  The root bound of the point settles every one off the cell boundary; NestQuantM has
+// no such bound, so there the word is decoded again.  LITERAL: the points on the boundary,
+// where Alg. 5's tie rules decide, take the literal test here, by the decode of their word (a
+// branch that few waves of phase 1 could skip, so phase 1 queues them).  |v| ct must be
+// within kE8BytesMax.
+template <bool LITERAL>
 __device__ __forceinline__ Verdict eval_bytes(const float (&v)[8], float ct, int t,
-                                              const EncodeArgs& a, E8Bytes& P, uint32_t& word) {
-  if (!nearest_e8_bytes(v, ct, P)) return EXACT;
+                                              const EncodeArgs& a, E8Bytes& X, uint32_t& word) {
+  if (!nearest_e8_bytes(v, ct, X)) return EXACT;
   const bool last = t == a.k - 1;
+  uint32_t xa, xb;   // X2 + 128 of the word
   if (a.decoder) {
     // outside the decoder's box the word means nothing, and its decode, which lies inside
-    // the box, differs from P
-    word = encode_e8_bytes<true>(P, a.q, a.mq);
-    uint32_t xa, xb;
+    // the box, differs from the point
+    word = encode_e8_bytes<true>(X, a.q, a.mq);
     decode_word_b8<true>(word, a.q, a.m2q, xa, xb);
-    const bool same = xa == P.a + 0x40404040u && xb == P.b + 0x40404040u;
+    const bool same = xa == X.a + 0x40404040u && xb == X.b + 0x40404040u;
     return same ? KEEP : (last ? EXACT : NEXT);
   }
-  const int M = e8_bytes_root_bound(P);
-  word = encode_e8_bytes(P, a.q, a.mq);
+  const int M = e8_bytes_root_bound(X);
+  if (M > 2 * a.q) return last ? EXACT : NEXT;
+  word = encode_e8_bytes<LITERAL>(X, a.q, a.mq);   // on the boundary |P_l - P_0| / 2 may be q
   if (M < 2 * a.q) return KEEP;
-  return last ? EXACT : (M > 2 * a.q ? NEXT : BOUNDARY);
+  if constexpr (!LITERAL) return BOUNDARY;
+  decode_word_b8<false>(word, a.q, a.m2q, xa, xb);
+  const bool same = xa == X.a + 0x40404040u && xb == X.b + 0x40404040u;
+  X.a = xa - 0x40404040u;
+  X.b = xb - 0x40404040u;
+  return same || last ? KEEP : NEXT;
 }
 
 // One evaluation of a queued block at beta t in the exact arithmetic: its nearest point P, and
@@ -610,14 +638,17 @@ __device__ __forceinline__ bool eval_exact(const float (&v)[8], float ct, int t,
 template <typename T> struct RawBlock { u32x4 w; };
 template <> struct RawBlock<float> { f32x4 a, b; };
 
-template <typename T>
+// NT: read once (streamed past the caches), else read again soon.
+template <typename T, bool NT>
 __device__ __forceinline__ void load_raw(const T* __restrict__ p, RawBlock<T>& r) {
-  r.w = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
-}
-template <>
-__device__ __forceinline__ void load_raw<float>(const float* __restrict__ p, RawBlock<float>& r) {
-  r.a = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(p));
-  r.b = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(p) + 1);
+  if constexpr (sizeof(T) == 4) {
+    const f32x4* q = reinterpret_cast<const f32x4*>(p);
+    r.a = NT ? __builtin_nontemporal_load(q) : q[0];
+    r.b = NT ? __builtin_nontemporal_load(q + 1) : q[1];
+  } else {
+    const u32x4* q = reinterpret_cast<const u32x4*>(p);
+    r.w = NT ? __builtin_nontemporal_load(q) : q[0];
+  }
 }
 template <typename T>
 __device__ __forceinline__ void zero_raw(RawBlock<T>& r) { r.w = u32x4{0u, 0u, 0u, 0u}; }
@@ -657,23 +688,14 @@ __device__ __forceinline__ void unpack_raw<_Float16>(const RawBlock<_Float16>& r
 // norm sqrt(2)) and M(y) = c M(x) up to relative rounding errors below 2^-19 (y, and the
 // fp32 evaluation of M), so M(x) > (2q + 2 sqrt(2) + 0.02) / (2 c (1 - 2^-12)) implies
 // M(P) > 2q.  With rb = fl64(r beta_t) and c = fl32(fl64(1 / rb)), 1 / c <= rb (1 + 2^-23),
-// so the threshold is evaluated from rb with products only (no division), inflated by 2^-20
-// to cover their roundings, and rounded up.  A threshold a little above the exact one only
-// lets a block try a beta that overloads; the search still ends at the same beta.
+// so the threshold is evaluated from rb with products only (no division), in fp32: the
+// 2^-19 covers its roundings (each below 2^-24) and 1 / (1 - 2^-12) - 1 - 2^-12.  A threshold a
+// little above the exact one only lets a block try a beta that overloads; the search still
+// ends at the same beta.  rb near fp32's underflow gets no threshold.
 // The NestQuantM counterpart for the statistic m_stat: (q + 2)(1 + 2^-12) / c.
-__device__ __forceinline__ float round_up_f32(double v) {
-  float f = (float)v;
-  if ((double)f < v) f = next_up(f);
-  return f;
-}
-
-__device__ __forceinline__ float skip_threshold_m(double rb, int q) {
-  return round_up_f32((double)(q + 2) * (1.0 + 0x1p-12) * rb * (1.0 + 0x1p-20));
-}
-
-__device__ __forceinline__ float skip_threshold(double rb, int q) {
-  return round_up_f32((2.0 * q + (double)kRootMargin) * (0.5 / (1.0 - 0x1p-12)) * rb *
-                      (1.0 + 0x1p-20));
+__device__ __forceinline__ float skip_threshold(double rb, int q, int decoder) {
+  const float k = decoder ? (float)(q + 2) : (float)q + 0.5f * kRootMargin;
+  return rb > 1e-30 ? (k * (1.0f + 0x1p-12f + 0x1p-19f)) * (float)rb : INFINITY;
 }
 
 // ROT (one row per workgroup only): the row is first rotated in LDS (rotate_rows_lds, the
@@ -685,26 +707,24 @@ template <typename T, int LANES, int BPT, bool TILES, bool ROT>
 // 976-982 against 991-997 us (two dwords of scratch in its fused instantiation).  The
 // 64-lane instantiation with one block per thread (rows of at most 64 blocks) gets the same
 // bound: its fused instantiation fits it without scratch.
-__global__ __launch_bounds__(LANES > 64 ? LANES : 256)
-__attribute__((amdgpu_waves_per_eu(LANES >= 128 || (LANES == 64 && BPT == 1) ? 5 : 1))) void encode_wave_kernel(
+__global__ __launch_bounds__((SlotMap<LANES, BPT>::NW * 64))
+__attribute__((amdgpu_waves_per_eu(LANES != 64 || BPT == 1 ? 5 : 1))) void encode_wave_kernel(
     const T* __restrict__ x, int64_t rows, int cols, int64_t ld_x, EncodeArgs a,
     uint32_t* __restrict__ codes, uint32_t* __restrict__ beta, float* __restrict__ scales) {
   using SM = SlotMap<LANES, BPT>;
   constexpr int SLOTS = SM::SLOTS;
   constexpr int RW = SM::ROWS_PER_WAVE;
-  constexpr int CW = SM::WGROW ? 1 : 4;          // row tables: per wave, or one per workgroup
-  constexpr int NW = (LANES > 64 ? LANES : 256) / 64;   // waves per workgroup: 4, or 2
-  static_assert(NW == 4 || NW == 2, "four or two waves per workgroup");
+  constexpr int NW = SM::NW;
+  constexpr int CW = SM::WGROW ? 1 : NW;         // row tables: per wave, or one per workgroup
   static_assert(!ROT || LANES == 256, "rotation in LDS needs one row per 256-lane workgroup");
-  __shared__ RawBlock<T> rawl[NW][ROT ? 1 : SLOTS];
+  // Blocks are staged in LDS, except by the one-wave workgroups of short rows, which read
+  // them again (from the caches): their LDS would be the bound on resident waves.
+  constexpr bool STAGED = NW > 1 && !ROT;
+  __shared__ RawBlock<T> rawl[NW][STAGED ? SLOTS : 1];
   __shared__ __attribute__((aligned(16))) float rbuf[ROT ? 8 * 4 * SLOTS : 1];
-  constexpr int BQ = SLOTS < 256 ? SLOTS : 256;   // room in the boundary list
-  __shared__ uint16_t queue[NW][SLOTS];
-  __shared__ uint16_t qnext[NW * SLOTS];
+  __shared__ uint16_t queue[NW][SLOTS];            // w << 12 | sl << 2 | t
+  __shared__ uint16_t qnext[NW > 1 ? NW * SLOTS : 1];
   __shared__ int qcnt[4];
-  __shared__ uint16_t bq[BQ];                      // boundary slots: w << 11 | sl << 2 | t
-  __shared__ uint2 bp[BQ];                         // and their points, as bytes P_l + 64
-  __shared__ int bcnt;
   __shared__ uint8_t tsl[NW][SLOTS];
   __shared__ float crow[CW][RW][4];
   __shared__ __attribute__((aligned(16))) float chi[CW][RW][4];
@@ -743,19 +763,24 @@ __attribute__((amdgpu_waves_per_eu(LANES >= 128 || (LANES == 64 && BPT == 1) ? 5
   const int nb = cols >> 3;
   const int nbw = (nb + 15) >> 4;
   auto row_base = [&](int w) -> int64_t {
-    return SM::WGROW ? bid : (bid * 4 + w) * RW;
+    return SM::WGROW ? bid : (bid * NW + w) * RW;
   };
   const int64_t row0 = row_base(wave);
-  const double n = (double)cols;
+  const double n = (double)cols, inv_n = 1.0 / n;
   // index of block j of row row_base(w) + rw in the code words: rows of more than 64 blocks
   // have rw = 0, shorter rows w RW + rw < 2^12 and nb <= 64, a 24-bit product
   auto code_at = [&](int w, int rw, int j) -> int64_t {
     if constexpr (SM::WGROW) return row_base(w) * nb + j;
-    return (bid * 4 * RW) * (int64_t)nb + __mul24(w * RW + rw, nb) + j;
+    return (bid * NW * RW) * (int64_t)nb + __mul24(w * RW + rw, nb) + j;
   };
   // block of slot sl of wave w, as fp32
   auto slot_block = [&](int w, int sl, float (&v)[8]) {
-    if constexpr (ROT) {
+    if constexpr (!STAGED && !ROT) {
+      RawBlock<T> raw;
+      load_raw<T, false>(x + (row_base(w) + SM::row_w(sl >> 6, sl & 63)) * ld_x +
+                             8 * SM::j(sl >> 6, sl & 63, w), raw);
+      unpack_raw<T>(raw, v);
+    } else if constexpr (ROT) {
       const int pe = lds_pos(8 * SM::j(sl >> 6, sl & 63, w));
 #pragma unroll
       for (int l = 0; l < 8; ++l) v[l] = rbuf[pe ^ l] * a.rot_s;
@@ -765,7 +790,6 @@ __attribute__((amdgpu_waves_per_eu(LANES >= 128 || (LANES == 64 && BPT == 1) ? 5
   };
 
   if (threadIdx.x < 4) qcnt[threadIdx.x] = 0;   // phase 2's list lengths, one per round
-  if (threadIdx.x == 0) bcnt = 0;
 
   // ---- phase 0: stage the slots in LDS, row sums of squares ----
   if constexpr (ROT) {
@@ -787,33 +811,39 @@ __attribute__((amdgpu_waves_per_eu(LANES >= 128 || (LANES == 64 && BPT == 1) ? 5
     part = wave_sum<64>(part);
     if (lane == 0) rsum[wave][0] = part;
   } else {
-    RawBlock<T> raw[BPT];
+    // up to FLY blocks of a lane in flight together
+    constexpr int FLY = BPT <= 8 ? BPT : 6;
+    static_assert(BPT % FLY == 0, "whole groups of loads");
     // one 64-bit row offset per lane; the rest of each block's address is uniform
     const T* __restrict__ x_lane = x + (row0 + SM::row_w(0, lane)) * ld_x;
-#pragma unroll
-    for (int i = 0; i < BPT; ++i) {
-      const int rw = SM::row_w(i, lane), j = SM::j(i, lane, wave);
-      const int64_t row = row0 + rw;
-      if (row < rows && j < nb) {
-        load_raw<T>(x_lane + SM::row_step(i) * ld_x + 8 * j, raw[i]);
-      } else {
-        zero_raw<T>(raw[i]);
-      }
-    }
     double part = 0.0;
 #pragma unroll
-    for (int i = 0; i < BPT; ++i) {
-      rawl[wave][i * 64 + lane] = raw[i];
-      float v[8];
-      unpack_raw<T>(raw[i], v);
-      double s = 0.0;
+    for (int i0 = 0; i0 < BPT; i0 += FLY) {
+      RawBlock<T> raw[FLY];
 #pragma unroll
-      for (int l = 0; l < 8; ++l) s = __builtin_fma((double)v[l], (double)v[l], s);
-      if constexpr (LANES < 64) {
-        s = wave_sum<LANES>(s);
-        if (lane % LANES == 0) rsum[wave][SM::row_w(i, lane)] = s;
-      } else {
-        part += s;
+      for (int u = 0; u < FLY; ++u) {
+        const int i = i0 + u, j = SM::j(i, lane, wave);
+        if (row0 + SM::row_w(i, lane) < rows && j < nb) {
+          load_raw<T, STAGED>(x_lane + SM::row_step(i) * ld_x + 8 * j, raw[u]);
+        } else {
+          zero_raw<T>(raw[u]);
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < FLY; ++u) {
+        const int i = i0 + u;
+        if constexpr (STAGED) rawl[wave][i * 64 + lane] = raw[u];
+        float v[8];
+        unpack_raw<T>(raw[u], v);
+        double s = 0.0;
+#pragma unroll
+        for (int l = 0; l < 8; ++l) s = __builtin_fma((double)v[l], (double)v[l], s);
+        if constexpr (LANES < 64) {
+          s = wave_sum<LANES>(s);
+          if (lane % LANES == 0) rsum[wave][SM::row_w(i, lane)] = s;
+        } else {
+          part += s;
+        }
       }
     }
     if constexpr (LANES >= 64) {
@@ -839,7 +869,7 @@ __attribute__((amdgpu_waves_per_eu(LANES >= 128 || (LANES == 64 && BPT == 1) ? 5
         for (int w = 1; w < NW; ++w) s += rsum[w][0];
       }
       bool sure;
-      float r = rms_candidate(s, n, sure);
+      float r = rms_candidate(s, n, inv_n, sure);
       if (!sure) {
         // rare: the double-double sum of the row, block by block from LDS
         double hi = 0.0, lo = 0.0;
@@ -862,8 +892,11 @@ __attribute__((amdgpu_waves_per_eu(LANES >= 128 || (LANES == 64 && BPT == 1) ? 5
       // later one (infinite from the last beta on).  Entry 3: the largest |x| the byte form
       // takes at the last beta; at the others the thresholds keep |y| below q + 3.
       float hi = INFINITY;
-      if (coded && t < 3 && t < a.k - 1) hi = a.decoder ? skip_threshold_m(rb, a.q) : skip_threshold(rb, a.q);
-      if (t == 3) hi = (float)((double)kE8BytesMax * (1.0 - 0x1p-16) * ((double)r * a.beta[a.k - 1]));
+      if (t < a.k - 1) hi = skip_threshold(rb, a.q, a.decoder);
+      if (t == 3) {
+        const double top = (double)r * a.beta[a.k - 1];
+        hi = top > 1e-30 ? (kE8BytesMax * (1.0f - 0x1p-16f)) * (float)top : 0.0f;
+      }
       chi[cw][rw][t] = hi;
       if (t == 0) {
         rrow[cw][rw] = coded ? r : 0.0f;
@@ -876,56 +909,52 @@ __attribute__((amdgpu_waves_per_eu(LANES >= 128 || (LANES == 64 && BPT == 1) ? 5
   // ---- phase 1: every slot at its predicted beta ----
   uint32_t* __restrict__ codes_w = codes + row0 * nb;   // this wave's rows
   int qn = 0;   // queue length, uniform over the wave
+  // blocks that are not staged: the next pass's, in flight while this one is evaluated
+  [[maybe_unused]] RawBlock<T> ahead;
+  [[maybe_unused]] const T* __restrict__ x_next = x + (row0 + SM::row_w(0, lane)) * ld_x + 8 * SM::j(0, lane, wave);
+  auto fetch = [&](int i) {
+    if constexpr (!STAGED && !ROT) {
+      zero_raw<T>(ahead);
+      if (i < BPT && row0 + SM::row_w(i, lane) < rows && SM::j(i, lane, wave) < nb)
+        load_raw<T, false>(x_next, ahead);
+      x_next += SM::RPP * ld_x;
+    }
+  };
+  fetch(0);
 #pragma unroll 1
   for (int i = 0; i < BPT; ++i) {
     const int sl = i * 64 + lane;
     const int rw = SM::row_w(i, lane), j = SM::j(i, lane, wave);
     const int64_t row = row0 + rw;
     const bool valid = row < rows && j < nb;
+    [[maybe_unused]] const RawBlock<T> now = ahead;
+    fetch(i + 1);
     const bool coded = valid && rrow[cw][rw] != 0.0f;
-    bool queued = false, bnd = false;
+    bool queued = false;
     int start = 0, t0 = 0;
     uint32_t word = 0u;
     E8Bytes P{0x40404040u, 0x40404040u};
     if (coded) {
       float v[8];
-      slot_block(wave, sl, v);
+      if constexpr (!STAGED && !ROT) {
+        unpack_raw<T>(now, v);
+      } else {
+        slot_block(wave, sl, v);
+      }
       // first beta whose point is not surely overloaded: one threshold test per beta
       const float mx = a.decoder ? m_stat(v) : root_bound_f(v);
       const f32x4 hi = *reinterpret_cast<const f32x4*>(chi[cw][rw]);
       t0 = mx > hi.x ? (mx > hi.y ? (mx > hi.z ? 3 : 2) : 1) : 0;
-      const Verdict vd = eval_bytes(v, crow[cw][rw][t0], t0, a, P, word);
-      // mx bounds every |x_l|: past hi.w the bytes may have wrapped
-      queued = vd == NEXT || vd == EXACT || mx > hi.w;
-      bnd = vd == BOUNDARY && !queued;
-      start = t0 + (vd == NEXT && !(mx > hi.w) ? 1 : 0);
-    }
-    // boundary points go to the boundary list with P (|P_l| <= 2q), while it has room, and
-    // to the queue at the same beta otherwise
-    const uint64_t lanes_below = (1ull << lane) - 1ull;
-    bool listed = false;
-    const uint64_t bmask = __ballot(bnd);
-    if (bmask != 0) {
-      int b0 = 0;
-      if (lane == 0) b0 = atomicAdd(&bcnt, __popcll(bmask));
-      b0 = __shfl(b0, 0, 64);
-      if (bnd) {
-        const int bi = b0 + __popcll(bmask & lanes_below);
-        if (bi < BQ) {
-          listed = true;
-          bq[bi] = (uint16_t)((wave << 11) | (sl << 2) | t0);
-          bp[bi] = uint2{P.a, P.b};
-        } else {
-          queued = true;
-          start = t0;
-        }
-      }
+      const Verdict vd = eval_bytes<false>(v, crow[cw][rw][t0], t0, a, P, word);
+      const bool past = mx > hi.w;   // mx bounds every |x_l|: the bytes may have wrapped
+      queued = vd != KEEP || past;
+      start = t0 + (vd == NEXT && !past ? 1 : 0);
     }
     const uint64_t mask = __ballot(queued);
     if (queued) {
-      const int pos = qn + __popcll(mask & lanes_below);
-      queue[wave][pos] = (uint16_t)((sl << 2) | start);
-    } else if (valid && !listed) {
+      const int pos = qn + __popcll(mask & ((1ull << lane) - 1ull));
+      queue[wave][pos] = (uint16_t)((wave << 12) | (sl << 2) | start);
+    } else if (valid) {
       codes_w[__mul24(rw, nb) + j] = word;   // rw = 0 or nb <= 64
       tsl[wave][sl] = (uint8_t)t0;
       // a point kept here is its own decode, X2 = P (zero for rows that are not coded)
@@ -933,83 +962,47 @@ __attribute__((amdgpu_waves_per_eu(LANES >= 128 || (LANES == 64 && BPT == 1) ? 5
     }
     qn += __popcll(mask);
   }
-  if (lane == 0) qlen[wave] = qn;
+  if (NW > 1 && lane == 0) qlen[wave] = qn;
   __syncthreads();
 
-  // ---- phase 2a: the boundary list, where P is known: the literal test alone ----
-  // A point that passes is coded at its beta; the others join their wave's queue at the
-  // next beta (each slot is in one list only, so the queues have room).
-  {
-    const int nbq = min(bcnt, BQ);
-    if (nbq > 0) {
-      for (int idx = threadIdx.x; idx < nbq; idx += NW * 64) {
-        const uint32_t e = bq[idx];
-        const int w = (int)(e >> 11), sl = (int)((e >> 2) & 511u), t = (int)(e & 3u);
-        const uint2 pb = bp[idx];
-        int P[8];
-#pragma unroll
-        for (int l = 0; l < 4; ++l) {
-          P[l] = (int)((pb.x >> (8 * l)) & 0xFFu) - 64;
-          P[4 + l] = (int)((pb.y >> (8 * l)) & 0xFFu) - 64;
-        }
-        if (!boundary_overloaded(P, a.q, a.mq, a.m2q)) {
-          const int i = sl >> 6, l = sl & 63;
-          const int rw = SM::row_w(i, l), j = SM::j(i, l, w);
-          const int64_t row = row_base(w) + rw;
-          const uint32_t word = encode_codes_amax(P, a.q, a.rq, a.mq, 2 * a.q);  // |P_l| <= 2q
-          codes[code_at(w, rw, j)] = word;
-          tsl[w][sl] = (uint8_t)t;
-          if constexpr (TILES) tile_from_x2(a, row, j, P, t);
-        } else {
-          const int pos = atomicAdd(&qlen[w], 1);
-          queue[w][pos] = (uint16_t)((sl << 2) | (t + 1));
-        }
-      }
-      __syncthreads();
-    }
-  }
-
   // ---- phase 2: the queued slots of the whole workgroup, one beta per round ----
-  // Round 0 takes the four wave queues; a slot whose point overloads goes on to the next
-  // beta in the next round, through a compacted list (entries w << 11 | sl << 2 | t), so
-  // that every round keeps its lanes busy instead of each wave looping until its slowest
-  // lane is done.  There are at most k rounds (t grows by one per round, and t = k - 1
-  // always stops).
+  // Round 0 takes the wave queues; a slot whose point overloads goes on to the next beta in
+  // the next round, through a compacted list, so that every round keeps its lanes busy
+  // instead of each wave looping until its slowest lane is done.  There are at most k rounds
+  // (t grows by one per round, and t = k - 1 always stops).  A workgroup of one wave
+  // compacts its queue in place (the wave writes entries it has already read) and meets no
+  // barrier that waits.
   {
     int qs[NW + 1];   // starts of the wave queues in round 0's index space
     qs[0] = 0;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) qs[w + 1] = qs[w] + qlen[w];
+    for (int w = 0; w < NW; ++w) qs[w + 1] = qs[w] + (NW > 1 ? qlen[w] : qn);
     int n = qs[NW];
 #pragma unroll 1
     for (int rd = 0; n > 0; ++rd) {
-      uint16_t* __restrict__ out_q = (rd & 1) ? &queue[0][0] : qnext;
-      const uint16_t* __restrict__ in_q = (rd & 1) ? qnext : &queue[0][0];
+      uint16_t* __restrict__ out_q = NW == 1 || (rd & 1) ? &queue[0][0] : qnext;
+      const uint16_t* __restrict__ in_q = NW > 1 && (rd & 1) ? qnext : &queue[0][0];
+      int nn = 0;       // the next round's length so far (one wave)
 #pragma unroll 1
       for (int base = 0; base < n; base += NW * 64) {
         const int idx = base + (int)threadIdx.x;
         bool more = false;
         uint32_t next = 0;
         if (idx < n) {
-          int w, sl, t;
-          if (rd == 0) {
-            int off;
-            if constexpr (NW == 4) {
-              w = (idx >= qs[1]) + (idx >= qs[2]) + (idx >= qs[3]);
-              off = w == 0 ? 0 : (w == 1 ? qs[1] : (w == 2 ? qs[2] : qs[3]));
-            } else {
-              w = idx >= qs[1];
-              off = w ? qs[1] : 0;
-            }
-            const uint32_t e = queue[w][idx - off];
-            sl = (int)(e >> 2);
-            t = (int)(e & 3u);
+          uint32_t e;
+          if (NW > 1 && rd == 0) {
+            int w = 0;
+#pragma unroll
+            for (int u = 1; u < NW; ++u) w += idx >= qs[u];
+            int off = 0;
+#pragma unroll
+            for (int u = 1; u < NW; ++u) off = w == u ? qs[u] : off;
+            e = queue[w][idx - off];
           } else {
-            const uint32_t e = in_q[idx];
-            w = (int)(e >> 11);
-            sl = (int)((e >> 2) & 511u);
-            t = (int)(e & 3u);
+            e = in_q[idx];
           }
+          const int w = NW > 1 ? (int)(e >> 12) : 0;
+          const int sl = (int)((e >> 2) & 1023u), t = (int)(e & 3u);
           const int i = sl >> 6, l = sl & 63;
           const int rw = SM::row_w(i, l), j = SM::j(i, l, w);
           const int64_t row = row_base(w) + rw;
@@ -1021,7 +1014,7 @@ __attribute__((amdgpu_waves_per_eu(LANES >= 128 || (LANES == 64 && BPT == 1) ? 5
                                       max3_abs(v[6], v[7], v[7]));
           E8Bytes Pb;
           uint32_t word;
-          const Verdict vd = vmax <= chi[c2][rw][3] ? eval_bytes(v, ct, t, a, Pb, word) : EXACT;
+          const Verdict vd = vmax <= chi[c2][rw][3] ? eval_bytes<true>(v, ct, t, a, Pb, word) : EXACT;
           if (vd == KEEP) {
             codes[code_at(w, rw, j)] = word;
             tsl[w][sl] = (uint8_t)t;
@@ -1045,20 +1038,24 @@ __attribute__((amdgpu_waves_per_eu(LANES >= 128 || (LANES == 64 && BPT == 1) ? 5
                 more = true;
               }
             }
-            next = ((uint32_t)w << 11) | ((uint32_t)sl << 2) | (uint32_t)(t + 1);
+            next = ((uint32_t)w << 12) | ((uint32_t)sl << 2) | (uint32_t)(t + 1);
           }
         }
         // wave-aggregated append to the next round's list
         const uint64_t mask = __ballot(more);
         if (mask != 0) {
-          int pos0 = 0;
-          if (lane == 0) pos0 = atomicAdd(&qcnt[rd], __popcll(mask));
-          pos0 = __shfl(pos0, 0, 64);
+          int pos0 = nn;
+          if constexpr (NW == 1) {
+            nn += __popcll(mask);
+          } else {
+            if (lane == 0) pos0 = atomicAdd(&qcnt[rd], __popcll(mask));
+            pos0 = __shfl(pos0, 0, 64);
+          }
           if (more) out_q[pos0 + __popcll(mask & ((1ull << lane) - 1ull))] = (uint16_t)next;
         }
       }
       __syncthreads();
-      n = qcnt[rd];
+      n = NW == 1 ? nn : qcnt[rd];
     }
   }
 
@@ -1102,8 +1099,8 @@ static hipError_t launch_w(const void* x, int64_t rows, int cols, int64_t ld_x,
                            const EncodeArgs& a, uint32_t* codes, uint32_t* beta, float* scales,
                            hipStream_t st) {
   using SM = SlotMap<LANES, BPT>;
-  constexpr int WG = LANES > 64 ? LANES : 256;
-  const int64_t rows_per_wg = SM::WGROW ? 1 : 4 * SM::ROWS_PER_WAVE;
+  constexpr int WG = SM::NW * 64;
+  const int64_t rows_per_wg = SM::WGROW ? 1 : SM::NW * SM::ROWS_PER_WAVE;
   int64_t grid = (rows + rows_per_wg - 1) / rows_per_wg;
   if (TILES && SM::WGROW) grid += a.task.wgs;
   hipLaunchKernelGGL((encode_wave_kernel<T, LANES, BPT, TILES, ROT>), dim3((unsigned)grid), dim3(WG), 0, st,
@@ -1138,13 +1135,17 @@ static hipError_t launch_dtype(const void* x, int64_t rows, int cols, int64_t ld
   }
 #define NQ_W(L, B) return launch_w<T, L, B, TILES>(x, rows, cols, ld_x, a, codes, beta, scales, st)
 #define NQ_L(L, B) return launch_t<T, L, B, false, TILES>(x, rows, cols, ld_x, a, codes, beta, scales, st)
-  // short rows: several rows per lane group, 256 blocks per wave when there are enough rows
-  // (with 512 the staged blocks took 51 KB of LDS per workgroup of fp16 rows, three
-  // workgroups per CU: the 2^21 x 128 fp16 matrix 555 against 509-511 us); rows of 33-64
-  // blocks have one row per wave, one block per lane
-  if (nb <= 8) { if (rows >= 2048) NQ_W(8, 4); NQ_W(8, 1); }
-  if (nb <= 16) { if (rows >= 1024) NQ_W(16, 4); NQ_W(16, 1); }
-  if (nb <= 32) { if (rows >= 512) NQ_W(32, 4); NQ_W(32, 1); }
+  // Short rows, one wave per workgroup: the more passes a wave takes, the fuller the lanes of
+  // its phase 2, as long as there are waves for every SIMD (rows of 128 fp16 entries, in
+  // us for 1, 4 and 12 passes: 16384 rows 11.4, 11.8, 23.4; 49152: 24.7, 17.7, 25.2; 200000:
+  // 82.8, 47.9, 53.2; 2^21: 839, 420, 385).
+#define NQ_S(L)                                            \
+  if (rows >= (64 / L) * (int64_t)12 * 16384) NQ_W(L, 12); \
+  if (rows >= (64 / L) * (int64_t)4 * 1024) NQ_W(L, 4);    \
+  NQ_W(L, 1)
+  if (nb <= 8) { NQ_S(8); }
+  if (nb <= 16) { NQ_S(16); }
+  if (nb <= 32) { NQ_S(32); }
   if (nb <= 64) NQ_W(64, 1);
   if (nb <= 128) NQ_W(64, 2);
   if (nb <= 256) NQ_W(64, 4);
@@ -1156,6 +1157,7 @@ static hipError_t launch_dtype(const void* x, int64_t rows, int cols, int64_t ld
   if (nb <= 4096) NQ_L(512, 8);
   NQ_L(1024, 0);
 #undef NQ_W
+#undef NQ_S
 #undef NQ_L
 }
 
