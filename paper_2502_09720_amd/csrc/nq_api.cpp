@@ -523,7 +523,6 @@ nq_status nq_encode_matmul(int32_t flags, const nq_params* pa, const void* x, nq
   //    decode-once path where its instantiation allows, W's tile decode rides in the same
   //    launch (workgroups after the encoder's, which fill the encoder's tail)
   const int nbp = tile_blocks(K, et);
-  const int64_t rows_p = M <= nq::kFusedMaxM ? (M + 15) / 16 * 16 : (M + 255) / 256 * 256;
   a.tiles = workspace;
   a.tile_et = et;
   a.nb_p = nbp;
@@ -538,7 +537,9 @@ nq_status nq_encode_matmul(int32_t flags, const nq_params* pa, const void* x, nq
   }
   hipError_t e = nq::launch_encode(x, (int)x_dtype, M, (int)K, ld_x, a, a_codes, a_beta,
                                    a_scales, st);
-  if (e == hipSuccess) e = nq::launch_tiles_pad(et, workspace, M, (int)(K / 8), rows_p, nbp, st);
+  // the padding columns alone: a row of A's tile reaches its own row of C only, and rows past
+  // M are not stored
+  if (e == hipSuccess) e = nq::launch_tiles_pad(et, workspace, M, (int)(K / 8), M, nbp, st);
   if (e != hipSuccess) return hip_status(e, who);
   // 2. decode W (unless the encoder's launch did) and contract
   return hip_status(launch_product(stages, et, pa, pw, A, W, K, c, ldc, workspace, st), who);

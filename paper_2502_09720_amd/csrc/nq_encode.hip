@@ -715,6 +715,7 @@ __attribute__((amdgpu_waves_per_eu(LANES != 64 || BPT == 1 ? 5 : 1))) void encod
   constexpr int SLOTS = SM::SLOTS;
   constexpr int RW = SM::ROWS_PER_WAVE;
   constexpr int NW = SM::NW;
+  constexpr bool CARRIES = SM::WGROW && LANES * BPT <= 1024;   // encode_carries_task
   constexpr int CW = SM::WGROW ? 1 : NW;         // row tables: per wave, or one per workgroup
   static_assert(!ROT || LANES == 256, "rotation in LDS needs one row per 256-lane workgroup");
   // Blocks are staged in LDS, except by the one-wave workgroups of short rows, which read
@@ -732,27 +733,16 @@ __attribute__((amdgpu_waves_per_eu(LANES != 64 || BPT == 1 ? 5 : 1))) void encod
   __shared__ double rsum[NW][RW];
   __shared__ int qlen[NW];
 
-  // A TileTask's a.task.wgs workgroups come last in the grid for rows of up to 1024 blocks:
-  // dispatched once every row has started, they fill the CUs that the encoder's last rows
-  // leave idle.  For longer rows (8 blocks per lane, many rounds of encoder workgroups) they
-  // come first.  Measured on the fused step: q_proj 98 (last) against 102.6 us (first),
-  // down_proj 546 (last) against 529 us (first), the 70B MLP 988 against 992 us; spreading
-  // them among the encoder's workgroups was slower in every case.
-  constexpr bool TASK_FIRST = BPT == 8;
-  int64_t bid = blockIdx.x;
-  if constexpr (TILES && SM::WGROW) {
-    if constexpr (TASK_FIRST) {
-      if (bid < a.task.wgs) {
-        run_tile_task<NW * 64>(a.task, a.tile_et, bid);
-        return;
-      }
-      bid -= a.task.wgs;
-    } else {
-      const int64_t first = (int64_t)gridDim.x - a.task.wgs;
-      if (bid >= first) {
-        run_tile_task<NW * 64>(a.task, a.tile_et, bid - first);
-        return;
-      }
+  // A TileTask's a.task.wgs workgroups come last in the grid: dispatched once every row has
+  // started, they fill the CUs that the encoder's last rows leave idle.  Measured on the
+  // fused step with bf16 tiles: q_proj 98 us (last) against 102.6 (first), the 70B MLP 988
+  // against 992; spreading them among the encoder's workgroups was slower.
+  const int64_t bid = blockIdx.x;
+  if constexpr (TILES && CARRIES) {
+    const int64_t first = (int64_t)gridDim.x - a.task.wgs;
+    if (bid >= first) {
+      run_tile_task<NW * 64>(a.task, a.tile_et, bid - first);
+      return;
     }
   }
   // the wave index is uniform over the wave: held in a scalar register, so that row offsets
@@ -1102,7 +1092,7 @@ static hipError_t launch_w(const void* x, int64_t rows, int cols, int64_t ld_x,
   constexpr int WG = SM::NW * 64;
   const int64_t rows_per_wg = SM::WGROW ? 1 : SM::NW * SM::ROWS_PER_WAVE;
   int64_t grid = (rows + rows_per_wg - 1) / rows_per_wg;
-  if (TILES && SM::WGROW) grid += a.task.wgs;
+  if (TILES && SM::WGROW && LANES * BPT <= 1024) grid += a.task.wgs;
   hipLaunchKernelGGL((encode_wave_kernel<T, LANES, BPT, TILES, ROT>), dim3((unsigned)grid), dim3(WG), 0, st,
                      (const T*)x, rows, cols, ld_x, a, codes, beta, scales);
   return hipGetLastError();

@@ -65,6 +65,10 @@ struct Cfg {
 using CfgMid = Cfg<256, 128, 4, 2, 3>;
 using CfgBig = Cfg<256, 256, 4, 2, 4, 64>;
 using CfgBigI8 = Cfg<256, 256, 4, 2, 2>;
+// Four-wave tiles for products whose tiles of the sizes above leave CUs idle.
+using Cfg128 = Cfg<128, 128, 2, 2, 3>;
+using Cfg12864 = Cfg<128, 64, 2, 2, 4>;
+using Cfg64 = Cfg<64, 64, 2, 2, 4>;
 }  // namespace gemm
 
 // One workgroup per TB blocks of the tile (tiles_block).
@@ -362,13 +366,42 @@ __global__ __launch_bounds__(C::NW * 64, 1) void gemm_kernel(
 }
 
 template <class C, int ET>
-static void launch_gemm(const u32x4* wa, const u32x4* ww, int kc, int64_t mp, int64_t np,
-                        const MatmulOperand& A, const MatmulOperand& W, float* c, int64_t ldc,
+static void launch_gemm(const u32x4* wa, const u32x4* ww, int kc, const MatmulOperand& A, const MatmulOperand& W, float* c, int64_t ldc,
                         float scale, hipStream_t st) {
-  const int tm = (int)(mp / C::BM), tn = (int)(np / C::BN);
+  // tiles of padding rows or columns alone are left out
+  const int tm = (int)((A.rows + C::BM - 1) / C::BM), tn = (int)((W.rows + C::BN - 1) / C::BN);
   hipLaunchKernelGGL((gemm_kernel<C, ET>), dim3((unsigned)(tm * tn)), dim3(C::NW * 64),
                      (size_t)C::NSTAGE * C::STAGE_BYTES, st, wa, ww, kc, tm, tn, A.scales,
                      W.scales, A.rows, W.rows, c, ldc, scale);
+}
+
+// The tile of an M x N product: the least rounds over the 256 CUs times what a round of one
+// tile per CU takes (us at K = 4096, int8, measured over the shapes below; the ratios hold
+// for the 16-bit types).  Large tiles read least from LDS and L2 per operation; small ones
+// fill the CUs when there are few.  Whole encode-and-multiply calls, us, by tile
+// (256x256, 256x128, 128x128, 128x64, 64x64):
+//   777 x 1024 x 4096 (rotated)  69 47 40 34 30     1000 x 4096 x 4096  70 49 43 49 49
+//   300 x 4096 x 4096            65 44 37 31 31     2048 x 4096 x 4096  76 62 69 80 80
+//   2048 x 14336 x 4096     156 168 189 226 227     2048 x 28672 x 8192 650 612 739 927 971
+//   4096 x 4096 x 14336     348 355 399 477 507
+static int pick_tile(int64_t M, int64_t N) {
+  struct Tile {
+    int bm, bn;
+    double us;
+  };
+  static const Tile tiles[5] = {
+      {256, 256, 45.0}, {256, 128, 25.0}, {128, 128, 20.0}, {128, 64, 13.0}, {64, 64, 7.5}};
+  int best = 0;
+  double least = 1e300;
+  for (int i = 0; i < 5; ++i) {
+    const int64_t n = ((M + tiles[i].bm - 1) / tiles[i].bm) * ((N + tiles[i].bn - 1) / tiles[i].bn);
+    const double us = (double)((n + 255) / 256) * tiles[i].us;
+    if (us < least) {
+      least = us;
+      best = i;
+    }
+  }
+  return best;
 }
 
 template <int ET>
@@ -377,7 +410,7 @@ static hipError_t decode_once(int stages, const MatmulOperand& A, const MatmulOp
                               hipStream_t st) {
   using namespace gemm;
   const int nb = (int)(K / 8);
-  const int64_t mp = (A.rows + 255) / 256 * 256;
+  const int64_t mp = (A.rows + 255) / 256 * 256;   // a multiple of every tile edge
   int64_t w_offset, np;
   int nbp;
   decode_once_layout(ET, A.rows, W.rows, K, w_offset, np, nbp);
@@ -394,14 +427,13 @@ static hipError_t decode_once(int stages, const MatmulOperand& A, const MatmulOp
     launch_tiles<ET>(W, nb, np, nbp, (void*)ww, st);
   }
   if (!(stages & 2)) return hipGetLastError();
-  // 256 x 256 tiles (half the global->LDS traffic per flop) unless they leave a partly
-  // empty last round over the 256 CUs that 256 x 128 tiles (half the work each) avoid
-  const int64_t big = (mp / 256) * (np / 256), mid = (mp / 256) * (np / 128);
-  if (big >= 256 && 2 * ((big + 255) / 256) <= (mid + 255) / 256) {
-    using Big = typename std::conditional<ET == ET_I8, CfgBigI8, CfgBig>::type;
-    launch_gemm<Big, ET>(wa, ww, kc, mp, np, A, W, c, ldc, scale, st);
-  } else {
-    launch_gemm<CfgMid, ET>(wa, ww, kc, mp, np, A, W, c, ldc, scale, st);
+  using Big = typename std::conditional<ET == ET_I8, CfgBigI8, CfgBig>::type;
+  switch (pick_tile(A.rows, W.rows)) {
+    case 0: launch_gemm<Big, ET>(wa, ww, kc, A, W, c, ldc, scale, st); break;
+    case 1: launch_gemm<CfgMid, ET>(wa, ww, kc, A, W, c, ldc, scale, st); break;
+    case 2: launch_gemm<Cfg128, ET>(wa, ww, kc, A, W, c, ldc, scale, st); break;
+    case 3: launch_gemm<Cfg12864, ET>(wa, ww, kc, A, W, c, ldc, scale, st); break;
+    default: launch_gemm<Cfg64, ET>(wa, ww, kc, A, W, c, ldc, scale, st); break;
   }
   return hipGetLastError();
 }
@@ -418,17 +450,22 @@ hipError_t launch_matmul_decode_once(int stages, int et, const MatmulOperand& A,
 
 hipError_t gemm_set_attributes() {
   using namespace gemm;
-  const void* k[6] = {(const void*)gemm_kernel<CfgMid, ET_BF16>, (const void*)gemm_kernel<CfgMid, ET_F16>,
-                      (const void*)gemm_kernel<CfgMid, ET_I8>, (const void*)gemm_kernel<CfgBig, ET_BF16>,
-                      (const void*)gemm_kernel<CfgBig, ET_F16>, (const void*)gemm_kernel<CfgBigI8, ET_I8>};
-  constexpr int mid = CfgMid::NSTAGE * CfgMid::STAGE_BYTES, big = CfgBig::NSTAGE * CfgBig::STAGE_BYTES;
-  constexpr int big8 = CfgBigI8::NSTAGE * CfgBigI8::STAGE_BYTES;
-  const int bytes[6] = {mid, mid, mid, big, big, big8};
-  for (int i = 0; i < 6; ++i) {
-    const hipError_t e = hipFuncSetAttribute(k[i], hipFuncAttributeMaxDynamicSharedMemorySize, bytes[i]);
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
+  hipError_t e = hipSuccess;
+  auto set = [&](const void* k, int bytes) {
+    if (e == hipSuccess) e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  };
+#define NQ_SET(C, ET) set((const void*)gemm_kernel<C, ET>, C::NSTAGE * C::STAGE_BYTES)
+#define NQ_SET3(C) NQ_SET(C, ET_BF16); NQ_SET(C, ET_F16); NQ_SET(C, ET_I8)
+  NQ_SET(CfgBig, ET_BF16);
+  NQ_SET(CfgBig, ET_F16);
+  NQ_SET(CfgBigI8, ET_I8);
+  NQ_SET3(CfgMid);
+  NQ_SET3(Cfg128);
+  NQ_SET3(Cfg12864);
+  NQ_SET3(Cfg64);
+#undef NQ_SET3
+#undef NQ_SET
+  return e;
 }
 
 }  // namespace nq

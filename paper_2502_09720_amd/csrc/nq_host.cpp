@@ -75,18 +75,25 @@ int rotation_split(int64_t n, int& p) {
   return 0;
 }
 
-// The encoder instantiations that carry a TileTask: First-beta rows of 257 to 2048 blocks
-// (one row per workgroup; every prefill shape of a Llama layer has K in 2056..16384).
-bool encode_carries_task(int cols, int strategy) {
+// The encoder instantiations with one row per workgroup: First-beta, 257 to 2048 blocks
+// (every prefill shape of a Llama layer has K in 2056..16384).
+static bool row_per_workgroup(int cols, int strategy) {
   const int nb = cols / 8;
   return strategy == 0 && nb > 256 && nb <= 2048;
 }
 
-// The same instantiations rotate their row in LDS, for widths nq_rotate supports:
-// 4096, 8192, 16384 and 28 * 2^k = 3584, 7168, 14336.
+// Those that carry a TileTask: rows of up to 1024 blocks.  Longer ones stage 32 KiB a
+// workgroup, so that few of the task's workgroups are resident beside them (4096 x 4096 x
+// 14336: 349 us carried, 327 in a launch of its own; 2048 x 4096 x 4096: 62 and 70).
+bool encode_carries_task(int cols, int strategy) {
+  return row_per_workgroup(cols, strategy) && cols / 8 <= 1024;
+}
+
+// Those that rotate their row in LDS, for widths nq_rotate supports: 4096, 8192, 16384 and
+// 28 * 2^k = 3584, 7168, 14336.
 bool encode_rotates(int cols, int strategy) {
   int p = 0;
-  return encode_carries_task(cols, strategy) && rotation_split(cols, p) != 0;
+  return row_per_workgroup(cols, strategy) && rotation_split(cols, p) != 0;
 }
 
 }  // namespace nq

@@ -1,0 +1,55 @@
+"""The tile sizes of the workspace product (M > 64): 256x256, 256x128, 128x128, 128x64 and
+64x64, picked by how many fill the CUs, each with whole and ragged edges, in every element type.
+
+Bar: the codes are drawn over all words and K is short, so every sum stays below 2^24 and is
+exact in each type; the rounding of the scales leaves an output within 4e-7 of the oracle's.
+"""
+
+import numpy as np
+import pytest
+
+from nq_gpu import upload_coded
+from oracle import layout, nestquant
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [
+    # (M, N, K): the tile that the rule takes
+    (65, 64, 72), (128, 130, 136), (777, 1024, 64),           # 64x64
+    (300, 4096, 72), (384, 4000, 136),                        # 128x64
+    (1000, 4096, 72), (1024, 4090, 64),                       # 128x128
+    (2048, 4096, 72), (1900, 4010, 136),                      # 256x128
+    (4096, 4096, 72), (4000, 4090, 64),                       # 256x256
+]
+TYPES = {   # q, k, mult, decoder
+    "i8": (14, 4, None, "full"),
+    "bf16": (16, 4, None, "m"),
+    "f16": (14, 4, (6, 8, 10, 16), "full"),
+}
+
+
+@pytest.mark.parametrize("et", list(TYPES))
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_tile_sizes(shape, et):
+    import torch
+    import paper_2502_09720_amd as nq
+    (M, N, K), (q, k, mult, decoder) = shape, TYPES[et]
+    rng = np.random.default_rng(M + 7 * N + K)
+    base = nestquant.default_base(q, k) if mult is None else 0.5 / q
+    ops, dev = [], []
+    for rows in (M, N):
+        c = rng.integers(0, q, (rows, K // 8, 8))
+        t = rng.integers(1, k + 1, (rows, K // 8))
+        r = rng.uniform(0.5, 2.0, rows).astype(np.float32)
+        ops.append((nestquant.integer_tiles(c, t, q, decoder, mult), r))
+        dev.append(upload_coded(layout.pack_codes(c), layout.pack_beta(t), r, rows, K, q, k,
+                                base, 1 if decoder == "m" else 0, mult=mult))
+    (TA, ra), (TW, rw) = ops
+    C = nestquant.product_from_tiles(TA, ra, base, TW, rw, base)
+    peak = (np.abs(TA).astype(np.float64) @ np.abs(TW).T.astype(np.float64)).max()
+    assert peak < 2 ** 24
+    out = torch.full((M, N + 8), 7.0, device="cuda")
+    got = nq.matmul(*dev, out=out[:, :N])
+    g = got.double().cpu().numpy()
+    assert np.all(np.abs(g - C) <= 4e-7 * np.abs(C))
+    assert bool((out[:, N:] == 7.0).all())
