@@ -60,7 +60,12 @@ __global__ __launch_bounds__(NWV * 64) void skinny_kernel(const u32x4* __restric
   constexpr bool I8 = ET == ET_I8;
   using Acc = typename std::conditional<I8, i32x4, f32x4>::type;
   constexpr int BPL = I8 ? 2 : 1;        // blocks per lane per step
-  constexpr int PD = MT <= 2 ? 8 : 4;    // steps per chunk
+  // steps per chunk: a chunk's A fragments and two sets of W's words stay in registers, and
+  // each wave has few chunks, so what hides the loads is the other waves.  int8: 4 steps (2
+  // for several row tiles) leave room for more of them than 8 (16 x 14336 x 4096 38.5 us
+  // against 40.3; 16 x 4096 x 14336 31.0 and 35.1, 32.2 at 2 steps; 64 x 28672 x 8192
+  // 161 at 4 and 146 at 2).
+  constexpr int PD = I8 ? (MT == 1 ? 4 : 2) : (MT <= 2 ? 8 : 4);
   constexpr int WPL = PD * BPL;          // code words per lane per chunk (8 or 16, or 4 / 8)
   constexpr int CB = 4 * WPL;            // blocks per chunk
   constexpr uint32_t OOB = 0x80000000u;  // beyond every range below
