@@ -50,6 +50,19 @@ void rotate_kernel(const T* __restrict__ x, int64_t rows, int n, int64_t ld_x, i
     }
     return;
   }
+  if (n != p && p >= kMixOut) {
+    // n = 28 p: the H_28 factor on the way out.  The outputs of a column go straight to
+    // memory (64 consecutive columns per wave and store), so nothing is written back to LDS
+    // and read again after a barrier (2048 x 14336 bf16: 44.8 us, 51.0 in place; 2048 x
+    // 28672: 102 and 136; a column's outputs dealt to two threads: 48.6).
+    for (int q = tid; q < rr * p; q += NT) {
+      const int r = rr == 1 ? 0 : q / p, b = q - r * p;
+      float* __restrict__ o = y + (row0 + r) * ld_y + b;
+      mix28_column(buf, b, r, p,
+                   [&](int a, float v) { __builtin_nontemporal_store(v * s, o + a * p); });
+    }
+    return;
+  }
   auto out = [&](int e, int r, int c) {
     const int pe = lds_pos(e);
     f32x4 lo = {buf[pe] * s, buf[pe ^ 1] * s, buf[pe ^ 2] * s, buf[pe ^ 3] * s};

@@ -142,21 +142,30 @@ __device__ __forceinline__ void fwht_pass_at(float* buf, int total, int lp, int 
 }
 
 // The H_28 factor for column b (< p) of row r of buf: output segment a is the sum over
-// i = 0..27, in increasing i, of H_28[i][a] X_i (27 additions per output).  Entry k of the
-// column is r n + k p + b = (28 r + k) p | b.
-__device__ __forceinline__ void mix28_column(float* buf, int b, int r, int p) {
+// i = 0..27, in increasing i, of H_28[i][a] X_i (27 additions per output), given to
+// put(a, sum).  Entry k of the column is r n + k p + b = (28 r + k) p | b.
+template <typename Put>
+__device__ __forceinline__ void mix28_column(const float* buf, int b, int r, int p, Put put) {
   const int pb = lds_pos(b);
-  auto at = [&](int k) -> float& { return buf[pb ^ lds_pos((28 * r + k) * p)]; };
   float x[28];
 #pragma unroll
-  for (int i = 0; i < 28; ++i) x[i] = at(i);
+  for (int i = 0; i < 28; ++i) x[i] = buf[pb ^ lds_pos((28 * r + i) * p)];
 #pragma unroll
   for (int a = 0; a < 28; ++a) {
     float acc = (kH28.neg[a] & 1u) != 0 ? -x[0] : x[0];
 #pragma unroll
     for (int i = 1; i < 28; ++i) acc = ((kH28.neg[a] >> i) & 1u) != 0 ? acc - x[i] : acc + x[i];
-    at(a) = acc;
+    put(a, acc);
   }
+}
+// Columns from which nq_rotate applies the factor on its way to memory: a store instruction
+// then writes whole 256-byte runs (224 entries, p = 8: 13.0 us that way, 11.7 through LDS).
+constexpr int kMixOut = 64;
+// In place.
+__device__ __forceinline__ void mix28_in_place(float* buf, int b, int r, int p) {
+  const int pb = lds_pos(b);
+  mix28_column(buf, b, r, p,
+                      [&](int a, float v) { buf[pb ^ lds_pos((28 * r + a) * p)] = v; });
 }
 
 // Steps 1 and 2 for the rr consecutive rows at x (n entries each, row stride ld_x), held in
@@ -166,7 +175,8 @@ __device__ __forceinline__ void mix28_column(float* buf, int b, int r, int p) {
 //
 // LAST_OUT (n = p = 2^lp with lp = 4, 8 or 12, where the last pass would hold a single
 // stage): that stage, h = p / 2, is left to the caller, which applies it as it reads the
-// entries out (rotate_last_stage); the function returns h then, else 0.
+// entries out; the function returns h then, else 0.  For n = 28 p with p >= kMixOut it leaves the
+// H_28 factor to the caller too.
 template <typename T, int NT = 256, bool LAST_OUT = false>
 __device__ __forceinline__ int rotate_rows_lds(const T* __restrict__ x, int64_t ld_x, int rr,
                                                int n, int p, int lp, float* buf) {
@@ -208,14 +218,14 @@ __device__ __forceinline__ int rotate_rows_lds(const T* __restrict__ x, int64_t 
   fwht_pass_at<11, NT>(buf, total, lp, top);
   __syncthreads();
   if (defer) return p / 2;
-  if (m == 28) {
+  if (m == 28 && !(LAST_OUT && p >= kMixOut)) {
     // the H_28 factor, column by column
     if (rr == 1) {
-      for (int b = tid; b < p; b += NT) mix28_column(buf, b, 0, p);
+      for (int b = tid; b < p; b += NT) mix28_in_place(buf, b, 0, p);
     } else {
       for (int q = tid; q < rr * p; q += NT) {
         const int r = q / p;
-        mix28_column(buf, q - r * p, r, p);
+        mix28_in_place(buf, q - r * p, r, p);
       }
     }
     __syncthreads();
