@@ -127,15 +127,16 @@ nq_status nq_decode(const nq_params* p, const uint32_t* codes, const uint32_t* b
  *   mult may differ between the operands; K must be the same);  K % 8 == 0, K <= 65536.
  *   c: device, M x N floats, row i at c + i*ldc, ldc >= N.
  * C_ij = r_Ai r_Wj base_A base_W / 4 * sum_blocks <m_A X2_A, m_W X2_W> (m = mult_t of the
- * block's beta); the integer tiles m*X2 are contracted with fp32 accumulation on bf16
- * matrix cores, exact in bf16 when 2q * mult_k <= 256 for both operands (always so for the
- * uniform grid), else on fp16 matrix cores (exact up to 2048, every allowed mult).
+ * block's beta); the integer tiles m*X2 are contracted as int8 with exact int32 sums where
+ * every m*X2 of both operands fits (nq_matmul_ex), else with fp32 accumulation on bf16 matrix
+ * cores, exact in bf16 when 2q * mult_k <= 256 for both operands (always so for the uniform
+ * grid), else on fp16 matrix cores (exact up to 2048, every allowed mult).
  * Each workgroup decodes (Alg. 2) the code words of its own rows of A and W into on-chip
  * memory and contracts them there, so the call needs and allocates no memory; a block of A is
- * decoded once per 128 columns of C (64 for M <= 64) and a block of W once per 256 rows of C
- * (64 for M <= 64).  nq_matmul_ex computes the same product decoding every block exactly
- * once into a caller's workspace, which is faster once M is in the hundreds; for M > 64 the
- * two sum in the same order and agree bit for bit. */
+ * decoded once per 64 or 128 columns of C and a block of W once per 64 to 256 rows of C.
+ * nq_matmul_ex computes the same product decoding every block exactly once into a caller's
+ * workspace, which is faster once M is in the hundreds; for M > 64 the two sum in the same
+ * order (or exactly) and agree bit for bit. */
 nq_status nq_matmul(const nq_params* pa, const uint32_t* a_codes, const uint32_t* a_beta,
                     const float* a_scales, int64_t M, const nq_params* pw,
                     const uint32_t* w_codes, const uint32_t* w_beta, const float* w_scales,

@@ -4,7 +4,7 @@
 // C = A_hat W_hat^T is Alg. 4 of the NestQuant paper for every pair of rows.  Here Alg. 2
 // (with Alg. 5) runs inside the product: for each stage of 8 blocks (64 values of K) the
 // threads of a workgroup fetch the code and beta words of the tile's BM + BN rows, decode
-// them into bf16 (or fp16) integers m * X2, exact, and store them in LDS with the swizzle of
+// them into int8 (or bf16, fp16) integers m * X2, exact, and store them in LDS with the swizzle of
 // the decode-once GEMM; the waves then multiply the stage on 32x32x16 matrix cores with fp32
 // accumulation, and the epilogue scales by r_Ai r_Wj base_A base_W / 4.  Two LDS buffers:
 // stage s + 1 is decoded while stage s is multiplied, and the code words of stage s + 2 are
@@ -27,24 +27,22 @@
 namespace nq {
 
 namespace fused {
-// BM x BN tile, WM x WN waves of (BM / WM) x (BN / WN) outputs; every stage holds 8 blocks
-// (128 bytes of 16-bit values) of each of the BM + BN rows.
+// BM x BN tile, WM x WN waves of (BM / WM) x (BN / WN) outputs; every stage holds 128 bytes of
+// each of the BM + BN rows: 8 blocks of 16-bit values, 16 of int8.
 template <int BM_, int BN_, int WM_, int WN_>
 struct Cfg {
   static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_;
   static constexpr int NW = WM * WN, NT = NW * 64;
   static constexpr int TM = BM / WM / 32, TN = BN / WN / 32;
-  static constexpr int SB = 128, CH = 8, BPS = 8;           // bytes, chunks, blocks per row
+  static constexpr int SB = 128, CH = 8;                    // bytes, 16-byte chunks per row
   static constexpr int STAGE_BYTES = (BM + BN) * SB;
-  static constexpr int ROWSTEP = NT / BPS;                  // rows covered by one pass
-  static constexpr int ITEMS = (BM + BN) / ROWSTEP;         // blocks per thread per stage
-  static constexpr int AITEMS = BM / ROWSTEP;               // the first AITEMS are A's
-  static_assert(BM % ROWSTEP == 0 && BN % ROWSTEP == 0, "rows must split evenly");
   static_assert(TM >= 1 && TN >= 1, "wave tiles of 32 x 32 at least");
   static_assert(2 * STAGE_BYTES <= 160 * 1024, "LDS is 160 KB");
 };
-using CfgLarge = Cfg<256, 128, 4, 2>;   // M > 64
-using CfgSmall = Cfg<64, 64, 2, 2>;     // M <= 64: more workgroups along N
+using CfgLarge = Cfg<256, 128, 4, 2>;
+using CfgMid = Cfg<128, 128, 2, 4>;
+using CfgWide = Cfg<64, 128, 2, 4>;
+using CfgSmall = Cfg<64, 64, 2, 2>;
 }  // namespace fused
 
 template <bool F16>
@@ -60,10 +58,13 @@ __global__ __launch_bounds__(C::NT, 1) void fused_kernel(MatmulOperand A, Matmul
                                                          int tn, float* __restrict__ c,
                                                          int64_t ldc, float scale) {
   constexpr int BM = C::BM, BN = C::BN, WM = C::WM, WN = C::WN, TM = C::TM, TN = C::TN;
-  constexpr int SB = C::SB, CH = C::CH, BPS = C::BPS, NT = C::NT;
-  constexpr int STAGE_BYTES = C::STAGE_BYTES, ROWSTEP = C::ROWSTEP;
-  constexpr int ITEMS = C::ITEMS, AITEMS = C::AITEMS;
-  constexpr bool F16 = ET == ET_F16;
+  constexpr bool F16 = ET == ET_F16, I8 = ET == ET_I8;
+  constexpr int SB = C::SB, CH = C::CH, NT = C::NT, BPS = I8 ? 16 : 8;   // blocks per stage
+  constexpr int STAGE_BYTES = C::STAGE_BYTES;
+  constexpr int ROWSTEP = NT / BPS;                         // rows covered by one pass
+  constexpr int ITEMS = (BM + BN) / ROWSTEP;                // blocks per thread per stage
+  constexpr int AITEMS = BM / ROWSTEP;                      // the first AITEMS are A's
+  static_assert(BM % ROWSTEP == 0 && BN % ROWSTEP == 0, "rows must split evenly");
   constexpr uint32_t OOB = 0x80000000u;   // beyond every buffer range below: reads 0
   extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
 
@@ -89,7 +90,7 @@ __global__ __launch_bounds__(C::NT, 1) void fused_kernel(MatmulOperand A, Matmul
       (void*)(W.beta + w0 * nbw), (short)0, wrows * nbw * 4, 0x00020000);
 
   // Item j of this thread: tile row lr + ROWSTEP j (A's rows first, then W's), block lb of
-  // each stage.  Eight consecutive threads read the eight consecutive words of one row.
+  // each stage.  BPS consecutive threads read the BPS consecutive words of one row.
   const int lr = tid / BPS, lb = tid % BPS;
   bool valid[ITEMS];
   uint32_t coff[ITEMS], boff[ITEMS];
@@ -101,7 +102,8 @@ __global__ __launch_bounds__(C::NT, 1) void fused_kernel(MatmulOperand A, Matmul
     valid[j] = r < (j < AITEMS ? arows : wrows);
     coff[j] = (uint32_t)(r * nb) * 4u;
     boff[j] = (uint32_t)(r * nbw) * 4u;
-    loff[j] = row * SB + ((lb ^ swz<CH>(row)) * 16);
+    loff[j] = I8 ? row * SB + (((lb >> 1) ^ swz<CH>(row)) * 16) + 8 * (lb & 1)
+                 : row * SB + ((lb ^ swz<CH>(row)) * 16);
   }
   uint32_t cw[ITEMS], bw[ITEMS];
   auto fetch = [&](int ks) {
@@ -129,6 +131,15 @@ __global__ __launch_bounds__(C::NT, 1) void fused_kernel(MatmulOperand A, Matmul
 #pragma unroll
     for (int j = 0; j < ITEMS; ++j) {
       if (!valid[j]) continue;
+      if constexpr (I8) {
+        const uint32_t mtab = j < AITEMS ? A.mtab : W.mtab;
+        const int dv = j < AITEMS ? dva : dvw, q = j < AITEMS ? A.q : W.q;
+        const uint32_t m2q = j < AITEMS ? A.m2q : W.m2q;
+        const int m = beta_mult(mtab, (bw[j] >> sh) & 3u);
+        *reinterpret_cast<u32x2*>(base + loff[j]) =
+            dv == 0 ? decode_tile_i8<0>(cw[j], m, q, m2q) : decode_tile_i8<1>(cw[j], m, q, m2q);
+        continue;
+      }
       u32x4 v;
       if (j < AITEMS) {
         v = decode16_dv<F16>(cw[j], beta_mult(A.mtab, (bw[j] >> sh) & 3u), A.q, A.m2q, dva);
@@ -139,7 +150,7 @@ __global__ __launch_bounds__(C::NT, 1) void fused_kernel(MatmulOperand A, Matmul
     }
   };
 
-  using Acc = f32x16;
+  using Acc = typename std::conditional<I8, i32x16, f32x16>::type;
   Acc acc[TM][TN];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
@@ -170,7 +181,11 @@ __global__ __launch_bounds__(C::NT, 1) void fused_kernel(MatmulOperand A, Matmul
       for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
-          if constexpr (F16) {
+          if constexpr (I8) {
+            acc[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(
+                __builtin_bit_cast(i32x4, af[i]), __builtin_bit_cast(i32x4, bfr[j]), acc[i][j],
+                0, 0, 0);
+          } else if constexpr (F16) {
             acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(
                 __builtin_bit_cast(f16x8, af[i]), __builtin_bit_cast(f16x8, bfr[j]), acc[i][j],
                 0, 0, 0);
@@ -219,7 +234,7 @@ __global__ __launch_bounds__(C::NT, 1) void fused_kernel(MatmulOperand A, Matmul
       for (int e = 0; e < 16; ++e) {
         const int r = i * 32 + 8 * (e >> 2) + (e & 3);
         if (m0 + r < M)
-          __builtin_nontemporal_store(acc[i][j][e] * (A.scales[m0 + r] * cs),
+          __builtin_nontemporal_store((float)acc[i][j][e] * (A.scales[m0 + r] * cs),
                                       &cp[r * ldc + j * 32]);
       }
   }
@@ -237,31 +252,76 @@ static hipError_t launch_fused_cfg(const MatmulOperand& A, const MatmulOperand& 
   return hipGetLastError();
 }
 
+// The tile of an M x N product: a workgroup's time is its decodes (BM + BN rows), so the fewest
+// rounds of small tiles over the 256 CUs wins while a CU has one or two, and large tiles,
+// which decode a row less often, beyond.  first + each * tiles per CU, us at K = 4096, fits
+// the int8 times below (K = 4096; 256x128, 128x128, 64x128, 64x64; the start's 256x128 and,
+// for M <= 64, 64x64 in bf16 last):
+//   300 x 4096   213 143  97 141 | 222      16 x 4096     80  74  71  69 |  89
+//   500 x 4096   212 143  98 141 | 222     512 x 14336   210 222 298 365 | 223
+//   100 x 4096   120 126  97 102 | 146    1500 x 4096    213 223 229 320 | 223
+static int pick_direct(int64_t M, int64_t N) {
+  struct Tile {
+    int bm, bn;
+    double first, each;
+  };
+  static const Tile tiles[4] = {
+      {256, 128, 0.0, 211.0}, {128, 128, 64.0, 79.0}, {64, 128, 25.0, 70.0}, {64, 64, 50.0, 44.0}};
+  int best = 0;
+  double least = 1e300;
+  for (int i = 0; i < 4; ++i) {
+    const int64_t n = ((M + tiles[i].bm - 1) / tiles[i].bm) * ((N + tiles[i].bn - 1) / tiles[i].bn);
+    const double us = tiles[i].first + (double)((n + 255) / 256) * tiles[i].each;
+    if (us < least) {
+      least = us;
+      best = i;
+    }
+  }
+  return best;
+}
+
+template <int ET>
+static hipError_t launch_fused_et(const MatmulOperand& A, const MatmulOperand& W, int64_t K,
+                                  float* c, int64_t ldc, float scale, hipStream_t st) {
+  using namespace fused;
+  switch (pick_direct(A.rows, W.rows)) {
+    case 0: return launch_fused_cfg<CfgLarge, ET>(A, W, K, c, ldc, scale, st);
+    case 1: return launch_fused_cfg<CfgMid, ET>(A, W, K, c, ldc, scale, st);
+    case 2: return launch_fused_cfg<CfgWide, ET>(A, W, K, c, ldc, scale, st);
+    default: return launch_fused_cfg<CfgSmall, ET>(A, W, K, c, ldc, scale, st);
+  }
+}
+
+// et is the 16-bit type that holds the tiles; int8 takes its place where they fit that (exact
+// sums, twice the matrix rate, and 10 instructions a block instead of 20 to form the tile).
 hipError_t launch_matmul_fused(int et, const MatmulOperand& A, const MatmulOperand& W,
                                int64_t K, float* c, int64_t ldc, float scale, hipStream_t st) {
-  using namespace fused;
-  const bool small = A.rows <= kFusedMaxM;
-  if (et == ET_F16)
-    return small ? launch_fused_cfg<CfgSmall, ET_F16>(A, W, K, c, ldc, scale, st)
-                 : launch_fused_cfg<CfgLarge, ET_F16>(A, W, K, c, ldc, scale, st);
-  return small ? launch_fused_cfg<CfgSmall, ET_BF16>(A, W, K, c, ldc, scale, st)
-               : launch_fused_cfg<CfgLarge, ET_BF16>(A, W, K, c, ldc, scale, st);
+  auto fits = [](const MatmulOperand& X) {
+    int m = 0;
+    for (int i = 0; i < 4; ++i) m = std::max(m, (int)((X.mtab >> (8 * i)) & 0xFFu));
+    return tiles_fit_i8(X.q, m, X.decoder);
+  };
+  if (fits(A) && fits(W)) return launch_fused_et<ET_I8>(A, W, K, c, ldc, scale, st);
+  if (et == ET_F16) return launch_fused_et<ET_F16>(A, W, K, c, ldc, scale, st);
+  return launch_fused_et<ET_BF16>(A, W, K, c, ldc, scale, st);
 }
 
 hipError_t fused_set_attributes() {
   using namespace fused;
-  const void* k[4] = {(const void*)fused_kernel<CfgLarge, ET_BF16>,
-                      (const void*)fused_kernel<CfgLarge, ET_F16>,
-                      (const void*)fused_kernel<CfgSmall, ET_BF16>,
-                      (const void*)fused_kernel<CfgSmall, ET_F16>};
-  const int bytes[4] = {2 * CfgLarge::STAGE_BYTES, 2 * CfgLarge::STAGE_BYTES,
-                        2 * CfgSmall::STAGE_BYTES, 2 * CfgSmall::STAGE_BYTES};
-  for (int i = 0; i < 4; ++i) {
-    const hipError_t e =
-        hipFuncSetAttribute(k[i], hipFuncAttributeMaxDynamicSharedMemorySize, bytes[i]);
-    if (e != hipSuccess) return e;
-  }
-  return hipSuccess;
+  hipError_t e = hipSuccess;
+  auto set = [&](const void* k, int bytes) {
+    if (e == hipSuccess) e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  };
+#define NQ_SET3(C)                                                       \
+  set((const void*)fused_kernel<C, ET_BF16>, 2 * C::STAGE_BYTES);        \
+  set((const void*)fused_kernel<C, ET_F16>, 2 * C::STAGE_BYTES);         \
+  set((const void*)fused_kernel<C, ET_I8>, 2 * C::STAGE_BYTES)
+  NQ_SET3(CfgLarge);
+  NQ_SET3(CfgMid);
+  NQ_SET3(CfgWide);
+  NQ_SET3(CfgSmall);
+#undef NQ_SET3
+  return e;
 }
 
 }  // namespace nq

@@ -1,5 +1,6 @@
-"""The tile sizes of the workspace product (M > 64): 256x256, 256x128, 128x128, 128x64 and
-64x64, picked by how many fill the CUs, each with whole and ragged edges, in every element type.
+"""The tile sizes of the workspace product (M > 64: 256x256, 256x128, 128x128, 128x64 and 64x64)
+and of the product without a workspace (256x128, 128x128, 64x128 and 64x64), picked by how many
+fill the CUs, each with whole and ragged edges, in every element type.
 
 Bar: the codes are drawn over all words and K is short, so every sum stays below 2^24 and is
 exact in each type; the rounding of the scales leaves an output within 4e-7 of the oracle's.
@@ -28,11 +29,30 @@ TYPES = {   # q, k, mult, decoder
 }
 
 
+DIRECT = [
+    (1, 64, 136), (100, 1000, 264),                           # 64x64
+    (300, 4096, 136), (500, 4090, 72),                        # 64x128
+    (600, 4096, 136), (640, 4090, 72),                        # 128x128
+    (1500, 4096, 136), (1536, 4090, 72),                      # 256x128
+]
+
+
 @pytest.mark.parametrize("et", list(TYPES))
 @pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
 def test_tile_sizes(shape, et):
-    import torch
     import paper_2502_09720_amd as nq
+    _check(nq.matmul, shape, et)
+
+
+@pytest.mark.parametrize("et", list(TYPES))
+@pytest.mark.parametrize("shape", DIRECT, ids=lambda s: "x".join(map(str, s)))
+def test_direct_tile_sizes(shape, et):
+    import paper_2502_09720_amd as nq
+    _check(nq.matmul_direct, shape, et)
+
+
+def _check(product, shape, et):
+    import torch
     (M, N, K), (q, k, mult, decoder) = shape, TYPES[et]
     rng = np.random.default_rng(M + 7 * N + K)
     base = nestquant.default_base(q, k) if mult is None else 0.5 / q
@@ -49,7 +69,7 @@ def test_tile_sizes(shape, et):
     peak = (np.abs(TA).astype(np.float64) @ np.abs(TW).T.astype(np.float64)).max()
     assert peak < 2 ** 24
     out = torch.full((M, N + 8), 7.0, device="cuda")
-    got = nq.matmul(*dev, out=out[:, :N])
+    got = product(*dev, out=out[:, :N])
     g = got.double().cpu().numpy()
     assert np.all(np.abs(g - C) <= 4e-7 * np.abs(C))
     assert bool((out[:, N:] == 7.0).all())
