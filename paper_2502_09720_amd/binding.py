@@ -5,6 +5,7 @@ the current stream's handle to the matching C entry point and checks its status.
 """
 
 import ctypes
+import functools
 import os
 from typing import NamedTuple
 
@@ -101,23 +102,33 @@ def default_base(q, k):
     return 10.0 / (k * q)
 
 
+@functools.lru_cache(maxsize=256)
+def _params_of(q, k, base, decoder, strategy, mult):
+    m = mult + (0,) * (4 - len(mult))
+    return _Params(q, k, base, decoder, strategy, (ctypes.c_int32 * 4)(*m))
+
+
 def _params(q, k, base, decoder=DECODER_FULL, strategy=FIRST_BETA, mult=None):
-    m = [0, 0, 0, 0]
-    if mult is not None:
-        m[:len(mult)] = [int(v) for v in mult]
-    return _Params(int(q), int(k), float(default_base(q, k) if base is None else base),
-                   int(decoder), int(strategy), (ctypes.c_int32 * 4)(*m))
+    """The nq_params of a call; the library only reads it, so equal ones are shared."""
+    return _params_of(int(q), int(k), float(default_base(q, k) if base is None else base),
+                      int(decoder), int(strategy),
+                      () if mult is None else tuple(int(v) for v in mult))
 
 
 def _stream(stream):
     import torch
     s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    return s.cuda_stream
+
+
+@functools.lru_cache(maxsize=None)
+def _dtype_codes():
+    import torch
+    return {torch.float32: NQ_F32, torch.float16: NQ_F16, torch.bfloat16: NQ_BF16}
 
 
 def _dtype_code(dt):
-    import torch
-    return {torch.float32: NQ_F32, torch.float16: NQ_F16, torch.bfloat16: NQ_BF16}[dt]
+    return _dtype_codes()[dt]
 
 
 def nq_codes_words(rows, cols):
@@ -159,10 +170,10 @@ def encode(x, q=14, k=4, base=None, stream=None, out=None, decoder=DECODER_FULL,
         raise ValueError("x must be a 2-D cuda tensor with unit column stride")
     rows, cols = x.shape
     lib = library()
-    nw, bw = lib.nq_codes_words(rows, cols), lib.nq_beta_words(rows, cols)
-    if nw < 0:
+    if cols < 8 or cols % 8:
         raise ValueError("cols must be a positive multiple of 8")
     if out is None:
+        nw, bw = lib.nq_codes_words(rows, cols), lib.nq_beta_words(rows, cols)
         codes = torch.empty(nw, dtype=torch.int32, device=x.device)
         beta = torch.empty(bw, dtype=torch.int32, device=x.device)
         scales = torch.empty(rows, dtype=torch.float32, device=x.device)
@@ -171,9 +182,9 @@ def encode(x, q=14, k=4, base=None, stream=None, out=None, decoder=DECODER_FULL,
     p = _params(q, k, base, decoder, strategy, mult)
 
     def call(fn, src):
-        return fn(ctypes.byref(p), ctypes.c_void_p(src.data_ptr()), _dtype_code(src.dtype), rows,
-                  cols, src.stride(0), ctypes.c_void_p(codes.data_ptr()),
-                  ctypes.c_void_p(beta.data_ptr()), ctypes.c_void_p(scales.data_ptr()),
+        return fn(ctypes.byref(p), src.data_ptr(), _dtype_code(src.dtype), rows,
+                  cols, src.stride(0), codes.data_ptr(),
+                  beta.data_ptr(), scales.data_ptr(),
                   _stream(stream))
     st = call(lib.nq_rotate_encode if rotate else lib.nq_encode, x)
     if rotate and st == NQ_ERR_UNSUPPORTED:
@@ -191,10 +202,10 @@ def decode(coded, out_dtype=None, stream=None, out=None):
         out = torch.empty(coded.rows, coded.cols, dtype=dt, device=coded.codes.device)
     p = _params(coded.q, coded.k, coded.base, coded.decoder, mult=coded.mult)
     lib = library()
-    _check(lib.nq_decode(ctypes.byref(p), ctypes.c_void_p(coded.codes.data_ptr()),
-                         ctypes.c_void_p(coded.beta.data_ptr()),
-                         ctypes.c_void_p(coded.scales.data_ptr()), coded.rows, coded.cols,
-                         ctypes.c_void_p(out.data_ptr()), _dtype_code(out.dtype), out.stride(0),
+    _check(lib.nq_decode(ctypes.byref(p), coded.codes.data_ptr(),
+                         coded.beta.data_ptr(),
+                         coded.scales.data_ptr(), coded.rows, coded.cols,
+                         out.data_ptr(), _dtype_code(out.dtype), out.stride(0),
                          _stream(stream)))
     return out
 
@@ -233,11 +244,11 @@ def matmul(a, w, stream=None, out=None, workspace=None, stages=STAGE_DECODE | ST
         if stream is not None:
             workspace.record_stream(stream)       # freed on return, in use on `stream`
     ws_ptr = workspace.data_ptr() if need > 0 else 0
-    args = (ctypes.byref(pa), ctypes.c_void_p(a.codes.data_ptr()),
-            ctypes.c_void_p(a.beta.data_ptr()), ctypes.c_void_p(a.scales.data_ptr()), a.rows,
-            ctypes.byref(pw), ctypes.c_void_p(w.codes.data_ptr()),
-            ctypes.c_void_p(w.beta.data_ptr()), ctypes.c_void_p(w.scales.data_ptr()), w.rows,
-            a.cols, ctypes.c_void_p(out.data_ptr()), out.stride(0), ctypes.c_void_p(ws_ptr),
+    args = (ctypes.byref(pa), a.codes.data_ptr(),
+            a.beta.data_ptr(), a.scales.data_ptr(), a.rows,
+            ctypes.byref(pw), w.codes.data_ptr(),
+            w.beta.data_ptr(), w.scales.data_ptr(), w.rows,
+            a.cols, out.data_ptr(), out.stride(0), ws_ptr,
             need, _stream(stream))
     if whole and not int8:
         _check(lib.nq_matmul_ex(*args))
@@ -257,10 +268,10 @@ def matmul_direct(a, w, stream=None, out=None):
     pa = _params(a.q, a.k, a.base, a.decoder, mult=a.mult)
     pw = _params(w.q, w.k, w.base, w.decoder, mult=w.mult)
     _check(library().nq_matmul(
-        ctypes.byref(pa), ctypes.c_void_p(a.codes.data_ptr()), ctypes.c_void_p(a.beta.data_ptr()),
-        ctypes.c_void_p(a.scales.data_ptr()), a.rows, ctypes.byref(pw),
-        ctypes.c_void_p(w.codes.data_ptr()), ctypes.c_void_p(w.beta.data_ptr()),
-        ctypes.c_void_p(w.scales.data_ptr()), w.rows, a.cols, ctypes.c_void_p(out.data_ptr()),
+        ctypes.byref(pa), a.codes.data_ptr(), a.beta.data_ptr(),
+        a.scales.data_ptr(), a.rows, ctypes.byref(pw),
+        w.codes.data_ptr(), w.beta.data_ptr(),
+        w.scales.data_ptr(), w.rows, a.cols, out.data_ptr(),
         out.stride(0), _stream(stream)))
     return out
 
@@ -301,13 +312,13 @@ def encode_matmul(x, w, q=14, k=4, base=None, decoder=DECODER_FULL, strategy=FIR
 
     def call(flags, src):
         return lib.nq_encode_matmul(
-            flags, ctypes.byref(pa), ctypes.c_void_p(src.data_ptr()), _dtype_code(src.dtype), M,
-            K, src.stride(0), ctypes.c_void_p(codes.data_ptr()),
-            ctypes.c_void_p(beta.data_ptr()), ctypes.c_void_p(scales.data_ptr()),
-            ctypes.byref(pw), ctypes.c_void_p(w.codes.data_ptr()),
-            ctypes.c_void_p(w.beta.data_ptr()), ctypes.c_void_p(w.scales.data_ptr()), w.rows,
-            ctypes.c_void_p(out.data_ptr()), out.stride(0),
-            ctypes.c_void_p(workspace.data_ptr() if need > 0 else 0), need, _stream(stream))
+            flags, ctypes.byref(pa), src.data_ptr(), _dtype_code(src.dtype), M,
+            K, src.stride(0), codes.data_ptr(),
+            beta.data_ptr(), scales.data_ptr(),
+            ctypes.byref(pw), w.codes.data_ptr(),
+            w.beta.data_ptr(), w.scales.data_ptr(), w.rows,
+            out.data_ptr(), out.stride(0),
+            workspace.data_ptr() if need > 0 else 0, need, _stream(stream))
     flags = CONTRACT_INT8 if int8 else 0
     st = call(flags | (ROTATE_A if rotate else 0), x)
     if rotate and st == NQ_ERR_UNSUPPORTED:
@@ -327,8 +338,8 @@ def rotate(x, out=None, stream=None):
     rows, cols = x.shape
     if out is None:
         out = torch.empty(rows, cols, dtype=torch.float32, device=x.device)
-    _check(library().nq_rotate(ctypes.c_void_p(x.data_ptr()), _dtype_code(x.dtype), rows, cols,
-                               x.stride(0), ctypes.c_void_p(out.data_ptr()), out.stride(0),
+    _check(library().nq_rotate(x.data_ptr(), _dtype_code(x.dtype), rows, cols,
+                               x.stride(0), out.data_ptr(), out.stride(0),
                                _stream(stream)))
     return out
 
@@ -358,9 +369,9 @@ def beta_stats(v, betas, q, decoder=DECODER_FULL, stream=None):
     mse = torch.empty(n, m, dtype=torch.float64, device=v.device)
     over = torch.empty(n, m, dtype=torch.uint8, device=v.device)
     b = (ctypes.c_double * m)(*[float(x) for x in betas])
-    _check(library().nq_beta_stats(int(q), int(decoder), ctypes.c_void_p(v.data_ptr()), n, b,
-                                   m, ctypes.c_void_p(mse.data_ptr()),
-                                   ctypes.c_void_p(over.data_ptr()), _stream(stream)))
+    _check(library().nq_beta_stats(int(q), int(decoder), v.data_ptr(), n, b,
+                                   m, mse.data_ptr(),
+                                   over.data_ptr(), _stream(stream)))
     return mse, over
 
 
@@ -381,8 +392,8 @@ def beta_dp(mse, over, k, stream=None, workspace=None):
         workspace = torch.empty(max(need, 8), dtype=torch.uint8, device=mse.device)
         if stream is not None:
             workspace.record_stream(stream)       # freed on return, in use on `stream`
-    _check(lib.nq_beta_dp(ctypes.c_void_p(mse.data_ptr()), ctypes.c_void_p(over.data_ptr()),
-                          n, m, int(k), ctypes.c_void_p(chosen.data_ptr()),
-                          ctypes.c_void_p(loss.data_ptr()), ctypes.c_void_p(workspace.data_ptr()),
+    _check(lib.nq_beta_dp(mse.data_ptr(), over.data_ptr(),
+                          n, m, int(k), chosen.data_ptr(),
+                          loss.data_ptr(), workspace.data_ptr(),
                           workspace.numel() * workspace.element_size(), _stream(stream)))
     return chosen, loss
