@@ -338,13 +338,15 @@ __device__ __forceinline__ void opt_block(const float (&v)[8], const float (&c)[
     } else {
       decode_word_b8<false>(w, a.q, a.m2q, xs[0], xs[1]);
     }
-    // a select chain, not an indexed read of the argument block (a memory load)
-    const double bt = t == 0 ? a.beta[0] : (t == 1 ? a.beta[1] : (t == 2 ? a.beta[2] : a.beta[3]));
+    // a select chain, not an indexed read of the argument block (a memory load); halved here,
+    // exactly (base > 2^-21), instead of after each of the eight products
+    const double hb =
+        0.5 * (t == 0 ? a.beta[0] : (t == 1 ? a.beta[1] : (t == 2 ? a.beta[2] : a.beta[3])));
     double err = 0.0;
 #pragma unroll
     for (int l = 0; l < 8; ++l) {
       const int x2 = (int)((xs[l >> 2] >> (8 * (l & 3))) & 0xFFu) - 128;
-      const double d = bt * (double)x2 / 2.0 - xn[l];
+      const double d = hb * (double)x2 - xn[l];
       err = err + d * d;
     }
     if (err < best) {
