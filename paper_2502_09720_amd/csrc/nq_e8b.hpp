@@ -17,6 +17,35 @@
 // |y| up to which every byte P_l + 64 stays in [4, 124] (|P_l| <= 2 (29 + 1/2) + 1).
 constexpr float kE8BytesMax = 29.0f;
 
+constexpr float kRootMargin = 2.8284272f + 0.02f;  // 2 sqrt(2), rounded up, + slack
+
+// The limits of a row on its blocks' entries, k rb with rb = fl64(r beta_t): products only (no
+// division), since for c = fl32(fl64(1 / rb)), 1 / c <= rb (1 + 2^-23).  In fp32 while the factors
+// are normal there, else in fp64 and one step up, so that the limits hold at every scale: a
+// block starts at the first beta whose threshold it does not pass, and at the betas below the
+// last it is that threshold which keeps |y| within kE8BytesMax.  (Limits a step too high are
+// harmless: that moves |x| c by less than 2^-20.)
+__device__ __forceinline__ float row_limit(float k, double rb) {
+  if (rb > 1e-30) return k * (float)rb;
+  return __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, (float)((double)k * rb)) + 1u);
+}
+
+// Factor of the threshold on the root bound M(x) of a block above which beta t surely
+// overloads: for the nearest point P of y = fl32(c x), M(P) >= 2 M(y) - 2 sqrt(2) (covering
+// radius 1, roots of norm sqrt(2)) and M(y) = c M(x) up to relative rounding errors below
+// 2^-19 (y, and the fp32 evaluation of M), so M(x) > (2q + 2 sqrt(2) + 0.02) / (2 c (1 - 2^-12))
+// implies M(P) > 2q.  The 2^-19 covers the threshold's own roundings (each below 2^-24) and
+// 1 / (1 - 2^-12) - 1 - 2^-12.  A threshold a little above the exact one only lets a block try a
+// beta that overloads; the search still ends at the same beta.
+// The NestQuantM counterpart for the statistic m_stat: (q + 2)(1 + 2^-12) / c.
+__device__ __forceinline__ float skip_factor(int q, int decoder) {
+  return (decoder ? (float)(q + 2) : (float)q + 0.5f * kRootMargin) *
+         (1.0f + 0x1p-12f + 0x1p-19f);
+}
+
+// Factor of the largest |x| whose products x c the byte form takes.
+constexpr float kBytesFactor = kE8BytesMax * (1.0f - 0x1p-16f);
+
 struct E8Bytes {
   uint32_t a, b;   // coordinates 0-3 and 4-7, byte l = P_l + 64
 };

@@ -19,7 +19,6 @@
 namespace nq {
 
 constexpr int a_max_k = 4;
-constexpr float kRootMargin = 2.8284272f + 0.02f;  // 2 sqrt(2), rounded up, + slack
 
 __device__ __forceinline__ float pick4(const float (&c)[4], int t) {
   return t == 0 ? c[0] : (t == 1 ? c[1] : (t == 2 ? c[2] : c[3]));
@@ -537,7 +536,7 @@ __global__ __launch_bounds__(LANES > 64 ? LANES : 256) void encode_kernel(
 // Phase 0 reads every slot from HBM (several of a lane's loads in flight together), stages it
 // in LDS (one-wave workgroups read it again instead) and forms the row sums of squares; then
 // a lane per row and beta turns the sum into the scale r, the multipliers c_t and the
-// thresholds of skip_threshold.  Phase 1 evaluates every slot, in the byte form, at the first
+// thresholds of row_limit.  Phase 1 evaluates every slot, in the byte form, at the first
 // beta the root bound of x does not rule out, and finishes it when its point is strictly
 // inside the cell (full decoder) or reproduced (NestQuantM).  The others are queued: points
 // that overload at the next beta, points on the cell boundary, at the last beta outside the
@@ -683,21 +682,6 @@ __device__ __forceinline__ void unpack_raw<_Float16>(const RawBlock<_Float16>& r
     v[2 * i] = (float)__builtin_bit_cast(_Float16, (uint16_t)(w[i] & 0xffffu));
     v[2 * i + 1] = (float)__builtin_bit_cast(_Float16, (uint16_t)(w[i] >> 16));
   }
-}
-
-// Threshold on the root bound M(x) of a block above which beta t surely overloads: for the
-// nearest point P of y = fl32(c x), M(P) >= 2 M(y) - 2 sqrt(2) (covering radius 1, roots of
-// norm sqrt(2)) and M(y) = c M(x) up to relative rounding errors below 2^-19 (y, and the
-// fp32 evaluation of M), so M(x) > (2q + 2 sqrt(2) + 0.02) / (2 c (1 - 2^-12)) implies
-// M(P) > 2q.  With rb = fl64(r beta_t) and c = fl32(fl64(1 / rb)), 1 / c <= rb (1 + 2^-23),
-// so the threshold is evaluated from rb with products only (no division), in fp32: the
-// 2^-19 covers its roundings (each below 2^-24) and 1 / (1 - 2^-12) - 1 - 2^-12.  A threshold a
-// little above the exact one only lets a block try a beta that overloads; the search still
-// ends at the same beta.  rb near fp32's underflow gets no threshold.
-// The NestQuantM counterpart for the statistic m_stat: (q + 2)(1 + 2^-12) / c.
-__device__ __forceinline__ float skip_threshold(double rb, int q, int decoder) {
-  const float k = decoder ? (float)(q + 2) : (float)q + 0.5f * kRootMargin;
-  return rb > 1e-30 ? (k * (1.0f + 0x1p-12f + 0x1p-19f)) * (float)rb : INFINITY;
 }
 
 // ROT (one row per workgroup only): the row is first rotated in LDS (rotate_rows_lds, the
@@ -881,14 +865,12 @@ __attribute__((amdgpu_waves_per_eu(LANES != 64 || BPT == 1 ? 5 : 1))) void encod
       const double rb = (double)r * a.beta[t];
       crow[cw][rw][t] = coded ? (float)(1.0 / rb) : 0.0f;
       // betas 0..2: the threshold above which a block surely overloads there and starts at a
-      // later one (infinite from the last beta on).  Entry 3: the largest |x| the byte form
-      // takes at the last beta; at the others the thresholds keep |y| below q + 3.
+      // later one (infinite from the last beta on); entry 3: the largest |x| the byte form
+      // takes at the last beta (the thresholds keep |y| below q + 3 at the others)
       float hi = INFINITY;
-      if (t < a.k - 1) hi = skip_threshold(rb, a.q, a.decoder);
-      if (t == 3) {
-        const double top = (double)r * a.beta[a.k - 1];
-        hi = top > 1e-30 ? (kE8BytesMax * (1.0f - 0x1p-16f)) * (float)top : 0.0f;
-      }
+      if (t == 3 || t < a.k - 1)
+        hi = row_limit(t == 3 ? kBytesFactor : skip_factor(a.q, a.decoder),
+                       t == 3 ? (double)r * a.beta[a.k - 1] : rb);
       chi[cw][rw][t] = hi;
       if (t == 0) {
         rrow[cw][rw] = coded ? r : 0.0f;

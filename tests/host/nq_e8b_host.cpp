@@ -81,3 +81,22 @@ extern "C" void nq_e8b_code(const int32_t* p, int64_t n, int q, int wide, int32_
     words[i] = wide ? nq::encode_e8_bytes<true>(P, q, mq) : nq::encode_e8_bytes<false>(P, q, mq);
   }
 }
+
+// The encoder's first evaluation of n blocks of a row of scale r: the beta it starts at (mx:
+// the statistic its thresholds bound, one per block) and the point there; ok[i] = 0 where the
+// block is left to the exact path.
+extern "C" void nq_e8b_first(const float* x, const float* mx, int64_t n, float r,
+                             const double* beta, int k, int q, int decoder, int32_t* t0,
+                             int32_t* p, uint8_t* ok) {
+  float hi[4];
+  const float skip = nq::skip_factor(q, decoder);
+  for (int t = 0; t < 3; ++t)
+    hi[t] = t < k - 1 ? nq::row_limit(skip, (double)r * beta[t]) : INFINITY;
+  hi[3] = nq::row_limit(nq::kBytesFactor, (double)r * beta[k - 1]);
+  for (int64_t i = 0; i < n; ++i) {
+    t0[i] = mx[i] > hi[0] ? (mx[i] > hi[1] ? (mx[i] > hi[2] ? 3 : 2) : 1) : 0;
+    const float c = (float)(1.0 / ((double)r * beta[t0[i]]));
+    nq_e8b_nearest(x + 8 * i, 1, c, p + 8 * i, ok + i);
+    if (mx[i] > hi[3]) ok[i] = 0;
+  }
+}

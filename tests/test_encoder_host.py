@@ -38,6 +38,9 @@ def lib(tmp_path_factory):
                                   ctypes.c_void_p, ctypes.c_void_p]
     so.nq_e8b_code.argtypes = [ctypes.c_void_p, ctypes.c_int64, ctypes.c_int, ctypes.c_int,
                                ctypes.c_void_p, ctypes.c_void_p]
+    so.nq_e8b_first.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_int64,
+                                ctypes.c_float, ctypes.c_void_p, ctypes.c_int, ctypes.c_int,
+                                ctypes.c_int] + [ctypes.c_void_p] * 3
     return so
 
 
@@ -100,6 +103,12 @@ def _root_bound(P):
     return np.concatenate([(P[i:i + 4096] @ ROOTS.T).max(1) for i in range(0, len(P), 4096)]) // 2
 
 
+def _root_bound_real(x):
+    """max over the roots of <x, root> (the bound of the point's integers, of reals)."""
+    _root_bound(np.zeros((1, 8), np.int64))
+    return (x.astype(np.float64) @ ROOTS.T.astype(np.float64)).max(1) / 2
+
+
 @pytest.mark.parametrize("wide", [0, 1])
 @pytest.mark.parametrize("q", list(range(2, 17)))
 def test_root_bound_and_code(lib, q, wide):
@@ -117,3 +126,54 @@ def test_root_bound_and_code(lib, q, wide):
     got = (words[take][:, None] >> (4 * np.arange(8, dtype=np.uint32))) & 15
     bad = np.nonzero(np.any(got != want, axis=1))[0]
     assert bad.size == 0, (q, P[take][bad[:2]], got[bad[:2]], want[bad[:2]])
+
+
+# The row's limits: which beta a block starts at and whether the byte form may take it there.
+# Scales at which r beta_1 and r beta_k lie on the two sides of 1e-30, where the thresholds
+# change their arithmetic, or near fp32's underflow, among ordinary ones.
+SCALES = [1.0, 1e30, 2e37, 5.6e-30, 5e-30, 3e-30, 1e-29, 2e-32, 1e-37, 2e-38]
+SETS = [   # q, k, multiples of 0.5 / q (None: the uniform grid)
+    (14, 4, None), (16, 4, None), (7, 2, None), (14, 1, None), (2, 4, None),
+    (14, 4, (4, 8, 16, 40)), (14, 4, (1, 4, 16, 64)), (16, 4, (1, 2, 3, 64)), (5, 2, (1, 64)),
+]
+
+
+@pytest.mark.parametrize("decoder", [0, 1])
+@pytest.mark.parametrize("q,k,mult", SETS, ids=lambda v: str(v).replace(" ", ""))
+def test_first_beta_of_any_scale(lib, q, k, mult, decoder):
+    """Blocks of up to 100 times the row scale: the beta that a block starts at is one that no
+    smaller beta's point would have been kept for, and a point the byte form settles is Alg. 5's."""
+    rng = np.random.default_rng(1000 * q + k)
+    n = 4000
+    z = rng.standard_normal((n, 8)) * rng.choice([0.05, 1.0], (n, 1))
+    z[np.arange(n), rng.integers(0, 8, n)] = np.where(
+        rng.random(n) < 0.5, -1, 1) * 10.0 ** rng.uniform(-1, 2, n)
+    beta = np.array([m * 0.5 / q for m in mult] if mult else
+                    [t * 10.0 / (k * q) for t in range(1, k + 1)])
+    for scale in SCALES:
+        r = np.float32(scale)
+        if 1.0 / (float(r) * beta[0]) > 3e38:
+            continue                         # no finite multiplier at the smallest beta
+        x = np.clip(z * float(r), -3e38, 3e38).astype(np.float32)
+        a = np.abs(x.astype(np.float64))
+        mx = _root_bound_real(x) if decoder == 0 else \
+            np.maximum(2 * a[:, 1:].max(1), a[:, 0])
+        mx = np.minimum(mx, 3.4e38).astype(np.float32)
+        t0, ok = np.empty(n, np.int32), np.empty(n, np.uint8)
+        p = np.empty((n, 8), np.int32)
+        lib.nq_e8b_first(x.ctypes.data, mx.ctypes.data, n, r, beta.ctypes.data, k, q, decoder,
+                         t0.ctypes.data, p.ctypes.data, ok.ctypes.data)
+        ok = ok.astype(bool)
+        assert t0.max() < k
+        kept = []
+        for b in beta:
+            y = (x * np.float32(1.0 / (float(r) * b))).astype(np.float64)
+            P = lattice.nearest_e8(y)
+            kept.append((P, ~voronoi.overloaded(P, q, "m" if decoder else "full")))
+        for t in range(k):
+            take = ok & (t0 == t)
+            bad = np.nonzero(np.any(p[take] != kept[t][0][take], axis=1))[0]
+            assert bad.size == 0, (scale, t, x[take][bad[:2]] / r, p[take][bad[:2]])
+            assert not np.any(kept[t][1] & (t0 > t)), (scale, t)
+        if scale == 1.0:
+            assert ok.mean() > 0.5

@@ -94,6 +94,63 @@ def test_encode_parity(nq, case):
     check_encode(nq, store, x32, dtype, q, k)
 
 
+# Row scales at which r beta_1 and r beta_k lie on the two sides of 1e-30 (where the encoder's
+# row limits change their arithmetic) or near fp32's underflow, with one entry of each 16
+# blocks far above the scale: such a block starts many times outside the first beta's cell.
+SMALL_SCALE_CASES = [
+    # (rows, cols, dtype, q, k, mult, decoder)
+    (90, 128, "f32", 14, 4, None, "full"),
+    (90, 1024, "bf16", 14, 4, None, "full"),
+    (24, 4096, "f32", 14, 4, None, "full"),
+    (24, 4096, "bf16", 14, 4, (1, 4, 16, 64), "full"),
+    (60, 256, "f32", 14, 4, (4, 8, 16, 40), "full"),
+    (60, 1024, "f32", 5, 2, (1, 64), "full"),
+    (60, 1024, "f32", 16, 4, None, "m"),
+    (24, 4096, "bf16", 16, 4, (1, 4, 16, 64), "m"),
+]
+
+
+def _small_scale_rows(rows, cols, dtype):
+    rng = np.random.default_rng(rows + cols)
+    x = rng.standard_normal((rows, cols))
+    for j in range(0, cols, 128):
+        x[:, j + 5] = 10.0 ** rng.uniform(0, 2, rows)
+    if cols >= 1024:
+        # a quarter of the rows: one block alone in its size, 20.2 to 20.8 times the scale,
+        # so that at the first default beta its point, wrapped to 8 bits, is a small one
+        i = np.arange(rows) % 8 >= 6
+        x[i, :] = rng.standard_normal((i.sum(), cols))
+        x[i, 24:32] *= 0.05
+        x[i, 30] = -rng.uniform(20.2, 20.8, i.sum()) * np.sqrt(cols / (cols - 425.0))
+    x /= np.sqrt((x ** 2).mean(1, keepdims=True))
+    x *= np.resize([1.0, 3e-30, 1e-29, 2e-30, 3e-37, 5.5e-30, 5e-30, 3e-30], rows)[:, None]
+    return workloads.round_to(x, dtype)
+
+
+@pytest.mark.parametrize("case", SMALL_SCALE_CASES,
+                         ids=lambda c: "-".join(str(v).replace(" ", "") for v in c))
+def test_encode_small_scales(nq, case):
+    rows, cols, dtype, q, k, mult, decoder = case
+    store, x32 = _small_scale_rows(rows, cols, dtype)
+    check_encode(nq, store, x32, dtype, q, k, base=None if mult is None else 0.5 / q,
+                 decoder=decoder, mult=mult)
+
+
+@pytest.mark.parametrize("rotate", [False, True])
+def test_encode_matmul_small_scales(nq, rotate):
+    """The tiles that the encoder writes for such rows are those of their codes."""
+    torch = __import__("torch")
+    store, _ = _small_scale_rows(70, 4096, "f32")
+    wstore, _ = workloads.random_rows(94, 80, 4096, dtype="bf16", scale=0.02)
+    w = nq.encode(to_device(wstore, "bf16"), q=14, k=4)
+    x = to_device(store, "f32")
+    a1 = nq.encode(x, q=14, k=4, rotate=rotate)
+    a2, c2 = nq.encode_matmul(x, w, q=14, k=4, rotate=rotate)
+    torch.cuda.synchronize()
+    assert torch.equal(a1.codes, a2.codes) and torch.equal(a1.beta, a2.beta)
+    assert torch.equal(nq.matmul(a1, w), c2)
+
+
 def test_encode_strided_rows(nq):
     store, x32 = workloads.random_rows(30, 17, 64, dtype="bf16")
     check_encode(nq, store, x32, "bf16", 14, 4, ld_pad=24)
