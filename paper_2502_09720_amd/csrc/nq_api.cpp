@@ -367,17 +367,12 @@ int64_t nq_matmul_workspace_size(int64_t M, int64_t N, int64_t K) {
   return (int64_t)nq::decode_once_workspace(M, N, K);
 }
 
-// The 16-bit element type of a product's tiles: bf16 while every |m X2| <= 256, else fp16
-// (exact up to 2048).
-static int elem_type16(const nq_params* pa, const nq_params* pw) {
-  return tile_bound(pa) <= 256 && tile_bound(pw) <= 256 ? nq::ET_BF16 : nq::ET_F16;
-}
-
-// Element type of the workspace product's tiles: int8 wherever every m X2 of both operands
-// fits it, else a 16-bit type.  All hold the integers exactly; int8 sums are exact too (int32)
-// and run at twice the matrix rate from half the bytes (contraction of 2048 x 4096 x 4096:
-// 62 us bf16, 39 us int8; of 4096 x 4096 x 14336: 353 and 197 us).  A request for int8 keeps
-// its bound of 127.
+// Element type of a product's tiles, the same for every entry point: int8 wherever every m X2
+// of both operands fits it, else bf16 while every |m X2| <= 256, else fp16 (exact up to 2048).
+// All hold the integers exactly; int8 sums are exact too (int32) and run at twice the matrix
+// rate from half the bytes (contraction of 2048 x 4096 x 4096: 62 us bf16, 39 us int8; of
+// 4096 x 4096 x 14336: 353 and 197 us; without a workspace also from 10 instructions a block
+// instead of 20).  A request for int8 keeps its bound of 127.
 static nq_status elem_type(const nq_params* pa, const nq_params* pw, bool i8, int& et,
                            const char* who) {
   if (i8 && (tile_bound(pa) > 127 || tile_bound(pw) > 127))
@@ -387,7 +382,9 @@ static nq_status elem_type(const nq_params* pa, const nq_params* pw, bool i8, in
   auto fits = [](const nq_params* p) {
     return nq::tiles_fit_i8(p->q, beta_mult(p, p->k - 1), p->decoder);
   };
-  et = fits(pa) && fits(pw) ? nq::ET_I8 : elem_type16(pa, pw);
+  et = fits(pa) && fits(pw) ? nq::ET_I8
+                            : (tile_bound(pa) <= 256 && tile_bound(pw) <= 256 ? nq::ET_BF16
+                                                                              : nq::ET_F16);
   return NQ_OK;
 }
 
@@ -479,6 +476,8 @@ nq_status nq_matmul(const nq_params* pa, const uint32_t* a_codes, const uint32_t
   if (nq_status s = check_matmul(pa, a_codes, a_beta, a_scales, M, pw, w_codes, w_beta,
                                  w_scales, N, K, c, ldc, who))
     return s;
+  int et = 0;
+  if (nq_status s = elem_type(pa, pw, false, et, who)) return s;
   if (M == 0 || N == 0) return ok();
   hipStream_t st = (hipStream_t)hip_stream;
   static PerDevice attrs(nq::fused_set_attributes);
@@ -489,7 +488,7 @@ nq_status nq_matmul(const nq_params* pa, const uint32_t* a_codes, const uint32_t
   nq::MatmulOperand W{w_codes, w_beta, w_scales, pw->q, nq::magic_2q(pw->q), N, pw->decoder,
                       mult_table(pw)};
   const float scale = (float)(pa->base * pw->base * 0.25);
-  return hip_status(nq::launch_matmul_fused(elem_type16(pa, pw), A, W, K, c, ldc, scale, st), who);
+  return hip_status(nq::launch_matmul_fused(et, A, W, K, c, ldc, scale, st), who);
 }
 
 

@@ -292,16 +292,9 @@ static hipError_t launch_fused_et(const MatmulOperand& A, const MatmulOperand& W
   }
 }
 
-// et is the 16-bit type that holds the tiles; int8 takes its place where they fit that (exact
-// sums, twice the matrix rate, and 10 instructions a block instead of 20 to form the tile).
 hipError_t launch_matmul_fused(int et, const MatmulOperand& A, const MatmulOperand& W,
                                int64_t K, float* c, int64_t ldc, float scale, hipStream_t st) {
-  auto fits = [](const MatmulOperand& X) {
-    int m = 0;
-    for (int i = 0; i < 4; ++i) m = std::max(m, (int)((X.mtab >> (8 * i)) & 0xFFu));
-    return tiles_fit_i8(X.q, m, X.decoder);
-  };
-  if (fits(A) && fits(W)) return launch_fused_et<ET_I8>(A, W, K, c, ldc, scale, st);
+  if (et == ET_I8) return launch_fused_et<ET_I8>(A, W, K, c, ldc, scale, st);
   if (et == ET_F16) return launch_fused_et<ET_F16>(A, W, K, c, ldc, scale, st);
   return launch_fused_et<ET_BF16>(A, W, K, c, ldc, scale, st);
 }

@@ -138,7 +138,7 @@ hipError_t launch_matmul_decode_once(int stages, int et, const MatmulOperand& A,
 hipError_t gemm_set_attributes();
 
 // No workspace (nq_matmul): each workgroup decodes its own rows' code words into LDS and
-// contracts them there (bf16 or fp16 tiles).
+// contracts them there (tiles of the ElemType et).
 hipError_t launch_matmul_fused(int et, const MatmulOperand& A, const MatmulOperand& W,
                                int64_t K, float* c, int64_t ldc, float scale, hipStream_t st);
 hipError_t fused_set_attributes();

@@ -67,3 +67,36 @@ def test_product_on_both_sides_of_the_int8_bound(case):
     for got in (nq.matmul(*dev), nq.matmul_direct(*dev)):
         g = got.double().cpu().numpy()
         assert np.all(np.abs(g - C) <= 4e-7 * np.abs(C))
+
+
+@pytest.mark.gpu
+def test_both_products_take_the_same_tiles():
+    """q = 16 with NestQuantM and three betas: every m X2 in use fits int8 (a fourth beta's
+    would not), with a workspace and without one.  Both then agree bit for bit and with the
+    oracle on sums that fp32 does not hold: rows of long points against near copies of
+    themselves, beyond 2^26 (inner products of 2E8 are multiples of 4)."""
+    import torch
+    import paper_2502_09720_amd as nq
+    M, N, K, q, k = 65, 70, 65536, 16, 3
+    rng = np.random.default_rng(k)
+    base = nestquant.default_base(q, k)
+    words = rng.integers(0, q, (1, 100000, 8))
+    X = nestquant.integer_tiles(words, np.ones((1, 100000), np.int64), q, "m").reshape(-1, 8)
+    longest = words[0][np.argsort(-(X.astype(np.int64) ** 2).sum(1))[:500]]
+    ca = longest[rng.integers(0, 500, (M, K // 8))]
+    cw = longest[rng.integers(0, 500, (N, K // 8))]
+    cw[:M] = np.where(rng.random((M, K // 8, 1)) < 0.02, cw[:M], ca)
+    ops, dev = [], []
+    for c in (ca, cw):
+        t = np.full(c.shape[:2], k)
+        r = rng.uniform(0.5, 2.0, len(c)).astype(np.float32)
+        ops.append((nestquant.integer_tiles(c, t, q, "m"), r))
+        dev.append(upload_coded(layout.pack_codes(c), layout.pack_beta(t), r, len(c), K, q, k,
+                                base, 1))
+    (TA, ra), (TW, rw) = ops
+    S = (TA.astype(np.int64) * TW[:M]).sum(1)
+    assert S.min() > 2 ** 26 and np.any(S % 8 != 0)
+    C = nestquant.product_from_tiles(TA, ra, base, TW, rw, base)
+    ex, direct = nq.matmul(*dev), nq.matmul_direct(*dev)
+    assert torch.equal(ex, direct)
+    assert np.all(np.abs(ex.double().cpu().numpy() - C) <= 4e-7 * np.abs(C))
