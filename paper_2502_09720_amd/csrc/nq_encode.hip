@@ -954,8 +954,9 @@ __attribute__((amdgpu_waves_per_eu(LANES != 64 || BPT == 1 ? 5 : 1))) void encod
     int n = qs[NW];
 #pragma unroll 1
     for (int rd = 0; n > 0; ++rd) {
-      uint16_t* __restrict__ out_q = NW == 1 || (rd & 1) ? &queue[0][0] : qnext;
-      const uint16_t* __restrict__ in_q = NW > 1 && (rd & 1) ? qnext : &queue[0][0];
+      // one array for a workgroup of one wave
+      uint16_t* out_q = NW == 1 || (rd & 1) ? &queue[0][0] : qnext;
+      const uint16_t* in_q = NW > 1 && (rd & 1) ? qnext : &queue[0][0];
       int nn = 0;       // the next round's length so far (one wave)
 #pragma unroll 1
       for (int base = 0; base < n; base += NW * 64) {
