@@ -367,24 +367,37 @@ int64_t nq_matmul_workspace_size(int64_t M, int64_t N, int64_t K) {
   return (int64_t)nq::decode_once_workspace(M, N, K);
 }
 
-// Element type of a product's tiles, the same for every entry point: int8 wherever every m X2
-// of both operands fits it, else bf16 while every |m X2| <= 256, else fp16 (exact up to 2048).
-// All hold the integers exactly; int8 sums are exact too (int32) and run at twice the matrix
-// rate from half the bytes (contraction of 2048 x 4096 x 4096: 62 us bf16, 39 us int8; of
-// 4096 x 4096 x 14336: 353 and 197 us; without a workspace also from 10 instructions a block
-// instead of 20).  A request for int8 keeps its bound of 127.
-static nq_status elem_type(const nq_params* pa, const nq_params* pw, bool i8, int& et,
-                           const char* who) {
-  if (i8 && (tile_bound(pa) > 127 || tile_bound(pw) > 127))
+// A product's operand.  Whether its tiles fit int8 is decided here, from the betas in use, for
+// every entry point.
+static nq::MatmulOperand operand(const nq_params* p, const uint32_t* codes,
+                                 const uint32_t* beta, const float* scales, int64_t rows) {
+  return {codes, beta, scales, p->q, nq::magic_2q(p->q), rows, p->decoder, mult_table(p),
+          nq::tiles_fit_i8(p->q, beta_mult(p, p->k - 1), p->decoder)};
+}
+
+// The 16-bit element type of a product's tiles: bf16 while every |m X2| <= 256, else fp16
+// (exact up to 2048).
+static int elem_type16(const nq_params* pa, const nq_params* pw) {
+  return tile_bound(pa) <= 256 && tile_bound(pw) <= 256 ? nq::ET_BF16 : nq::ET_F16;
+}
+
+// Element type of a product's tiles: int8 wherever every m X2 of both operands fits it, else a
+// 16-bit type.  All hold the integers exactly; int8 sums are exact too (int32) and run at
+// twice the matrix rate from half the bytes (contraction of 2048 x 4096 x 4096: 62 us bf16,
+// 39 us int8; of 4096 x 4096 x 14336: 353 and 197 us; without a workspace also from 10
+// instructions a block instead of 20).
+static int elem_type(const nq_params* pa, const nq_params* pw, const nq::MatmulOperand& A,
+                     const nq::MatmulOperand& W) {
+  return A.fits_i8 && W.fits_i8 ? nq::ET_I8 : elem_type16(pa, pw);
+}
+
+// A request for int8 keeps its bound of 127.
+static nq_status check_int8(int32_t flags, const nq_params* pa, const nq_params* pw,
+                            const char* who) {
+  if ((flags & NQ_CONTRACT_INT8) && (tile_bound(pa) > 127 || tile_bound(pw) > 127))
     return fail(NQ_ERR_UNSUPPORTED,
                 "%s: the int8 contraction needs 2q * mult_k <= 127 for both operands (k * q <= "
                 "63 on the uniform grid; |m X2| must fit int8)", who);
-  auto fits = [](const nq_params* p) {
-    return nq::tiles_fit_i8(p->q, beta_mult(p, p->k - 1), p->decoder);
-  };
-  et = fits(pa) && fits(pw) ? nq::ET_I8
-                            : (tile_bound(pa) <= 256 && tile_bound(pw) <= 256 ? nq::ET_BF16
-                                                                              : nq::ET_F16);
   return NQ_OK;
 }
 
@@ -434,16 +447,13 @@ nq_status nq::matmul_stages(int32_t stages, const nq_params* pa, const uint32_t*
   if (nq_status s = check_matmul(pa, a_codes, a_beta, a_scales, M, pw, w_codes, w_beta,
                                  w_scales, N, K, c, ldc, who))
     return s;
-  int et = 0;
-  if (nq_status s = elem_type(pa, pw, (stages & NQ_CONTRACT_INT8) != 0, et, who)) return s;
+  if (nq_status s = check_int8(stages, pa, pw, who)) return s;
   if (M == 0 || N == 0) return ok();
   if (nq_status s = check_workspace(M, N, K, workspace, workspace_bytes, who)) return s;
-  nq::MatmulOperand A{a_codes, a_beta, a_scales, pa->q, nq::magic_2q(pa->q), M, pa->decoder,
-                      mult_table(pa)};
-  nq::MatmulOperand W{w_codes, w_beta, w_scales, pw->q, nq::magic_2q(pw->q), N, pw->decoder,
-                      mult_table(pw)};
-  return hip_status(launch_product(stages, et, pa, pw, A, W, K, c, ldc, workspace,
-                                   (hipStream_t)hip_stream),
+  const nq::MatmulOperand A = operand(pa, a_codes, a_beta, a_scales, M);
+  const nq::MatmulOperand W = operand(pw, w_codes, w_beta, w_scales, N);
+  return hip_status(launch_product(stages, elem_type(pa, pw, A, W), pa, pw, A, W, K, c, ldc,
+                                   workspace, (hipStream_t)hip_stream),
                     who);
 }
 
@@ -476,19 +486,15 @@ nq_status nq_matmul(const nq_params* pa, const uint32_t* a_codes, const uint32_t
   if (nq_status s = check_matmul(pa, a_codes, a_beta, a_scales, M, pw, w_codes, w_beta,
                                  w_scales, N, K, c, ldc, who))
     return s;
-  int et = 0;
-  if (nq_status s = elem_type(pa, pw, false, et, who)) return s;
   if (M == 0 || N == 0) return ok();
   hipStream_t st = (hipStream_t)hip_stream;
   static PerDevice attrs(nq::fused_set_attributes);
   const hipError_t attr_err = attrs.ensure(st);
   if (attr_err != hipSuccess) return hip_status(attr_err, who);
-  nq::MatmulOperand A{a_codes, a_beta, a_scales, pa->q, nq::magic_2q(pa->q), M, pa->decoder,
-                      mult_table(pa)};
-  nq::MatmulOperand W{w_codes, w_beta, w_scales, pw->q, nq::magic_2q(pw->q), N, pw->decoder,
-                      mult_table(pw)};
+  const nq::MatmulOperand A = operand(pa, a_codes, a_beta, a_scales, M);
+  const nq::MatmulOperand W = operand(pw, w_codes, w_beta, w_scales, N);
   const float scale = (float)(pa->base * pw->base * 0.25);
-  return hip_status(nq::launch_matmul_fused(et, A, W, K, c, ldc, scale, st), who);
+  return hip_status(nq::launch_matmul_fused(elem_type16(pa, pw), A, W, K, c, ldc, scale, st), who);
 }
 
 
@@ -509,15 +515,13 @@ nq_status nq_encode_matmul(int32_t flags, const nq_params* pa, const void* x, nq
   if (nq_status s = check_matmul(pa, a_codes, a_beta, a_scales, M, pw, w_codes, w_beta,
                                  w_scales, N, K, c, ldc, who))
     return s;
-  int et = 0;
-  if (nq_status s = elem_type(pa, pw, (flags & NQ_CONTRACT_INT8) != 0, et, who)) return s;
+  if (nq_status s = check_int8(flags, pa, pw, who)) return s;
   if (M == 0 || N == 0) return ok();
   if (nq_status s = check_workspace(M, N, K, workspace, workspace_bytes, who)) return s;
   hipStream_t st = (hipStream_t)hip_stream;
-  nq::MatmulOperand A{a_codes, a_beta, a_scales, pa->q, nq::magic_2q(pa->q), M, pa->decoder,
-                      mult_table(pa)};
-  nq::MatmulOperand W{w_codes, w_beta, w_scales, pw->q, nq::magic_2q(pw->q), N, pw->decoder,
-                      mult_table(pw)};
+  const nq::MatmulOperand A = operand(pa, a_codes, a_beta, a_scales, M);
+  const nq::MatmulOperand W = operand(pw, w_codes, w_beta, w_scales, N);
+  const int et = elem_type(pa, pw, A, W);
   // 1. encode A; the encoder also writes A's decoded tiles into the workspace and, on the
   //    decode-once path where its instantiation allows, W's tile decode rides in the same
   //    launch (workgroups after the encoder's, which fill the encoder's tail)

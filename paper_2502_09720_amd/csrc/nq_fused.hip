@@ -294,7 +294,7 @@ static hipError_t launch_fused_et(const MatmulOperand& A, const MatmulOperand& W
 
 hipError_t launch_matmul_fused(int et, const MatmulOperand& A, const MatmulOperand& W,
                                int64_t K, float* c, int64_t ldc, float scale, hipStream_t st) {
-  if (et == ET_I8) return launch_fused_et<ET_I8>(A, W, K, c, ldc, scale, st);
+  if (A.fits_i8 && W.fits_i8) return launch_fused_et<ET_I8>(A, W, K, c, ldc, scale, st);
   if (et == ET_F16) return launch_fused_et<ET_F16>(A, W, K, c, ldc, scale, st);
   return launch_fused_et<ET_BF16>(A, W, K, c, ldc, scale, st);
 }

@@ -78,6 +78,7 @@ struct MatmulOperand {
   int64_t rows;
   int decoder;
   uint32_t mtab;   // byte i: the multiple m of base for beta index i (beta = m * base)
+  bool fits_i8;    // every m X2 of the betas in use fits int8 (tiles_fit_i8)
 };
 
 // Element type of the decoded tiles m * X2 and of the matrix-core instructions: bf16 holds
@@ -138,7 +139,7 @@ hipError_t launch_matmul_decode_once(int stages, int et, const MatmulOperand& A,
 hipError_t gemm_set_attributes();
 
 // No workspace (nq_matmul): each workgroup decodes its own rows' code words into LDS and
-// contracts them there (tiles of the ElemType et).
+// contracts them there, in int8 where both operands fit it, else in the 16-bit type et.
 hipError_t launch_matmul_fused(int et, const MatmulOperand& A, const MatmulOperand& W,
                                int64_t K, float* c, int64_t ldc, float scale, hipStream_t st);
 hipError_t fused_set_attributes();
