@@ -542,7 +542,7 @@ nq_status nq_encode_matmul(int32_t flags, const nq_params* pa, const void* x, nq
                                    a_scales, st);
   // the padding columns alone: a row of A's tile reaches its own row of C only, and rows past
   // M are not stored
-  if (e == hipSuccess) e = nq::launch_tiles_pad(et, workspace, M, (int)(K / 8), M, nbp, st);
+  if (e == hipSuccess) e = nq::launch_tiles_pad(et, workspace, M, (int)(K / 8), nbp, st);
   if (e != hipSuccess) return hip_status(e, who);
   // 2. decode W (unless the encoder's launch did) and contract
   return hip_status(launch_product(stages, et, pa, pw, A, W, K, c, ldc, workspace, st), who);

@@ -156,8 +156,8 @@ __device__ __forceinline__ float med3_abs(float m1, float m2, float a) {
 // max over the 240 roots lambda of E8 of <P, lambda> for P in 2E8 units:
 // max( |P|_(1) + |P|_(2),  (sum |P_i| - 2 [odd number of negative P_i] min |P_i|) / 2 ).
 // P lies strictly inside the cell q V of q 2E8 iff the bound is < 2q, strictly outside iff
-// it is > 2q; equality is the cell boundary.  amax = |P|_(1) comes with it.
-__device__ __forceinline__ int e8_root_bound(const int (&P)[8], int& amax) {
+// it is > 2q; equality is the cell boundary.
+__device__ __forceinline__ int e8_root_bound(const int (&P)[8]) {
   int a[8];
 #pragma unroll
   for (int l = 0; l < 8; ++l) a[l] = abs(P[l]);
@@ -170,13 +170,7 @@ __device__ __forceinline__ int e8_root_bound(const int (&P)[8], int& amax) {
   const int sa = ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
   const int mn = min(min(min(a[0], a[1]), min(a[2], a[3])), min(min(a[4], a[5]), min(a[6], a[7])));
   const int neg = (int)(((uint32_t)(P[0] ^ P[1] ^ P[2] ^ P[3] ^ P[4] ^ P[5] ^ P[6] ^ P[7])) >> 31);
-  amax = m1;
   return max(m1 + m2, (sa - ((0 - neg) & (mn << 1))) >> 1);   // a select, not a multiply
-}
-
-__device__ __forceinline__ int e8_root_bound(const int (&P)[8]) {
-  int amax;
-  return e8_root_bound(P, amax);
 }
 
 // Root bound of a real 8-vector: max over the 240 roots lambda of <x, lambda>.  For the
@@ -213,7 +207,6 @@ __device__ __forceinline__ int mod_q_general(int v, int q, float rq) {
 // Fast path (|P_i| < 512, always true for points that do not overload, |P_i| <= 2q): add a
 // bias of 1024 q to make v non-negative and divide with a 24-bit multiply,
 // floor(u / q) = (u * mq) >> 20 with mq = ceil(2^20 / q), exact for u < 2^20 / q.
-// encode_codes_amax takes max |P_i| when the caller already has it.
 //
 // umul24_v is the full-rate 24-bit multiply (low 32 bits of the product of the operands'
 // low 24 bits), the same as __umul24; written out because the compiler turns some
@@ -249,8 +242,10 @@ __device__ __forceinline__ uint32_t bcnt_add(uint32_t x, uint32_t acc) {
   return r;
 }
 
-__device__ __forceinline__ uint32_t encode_codes_amax(const int (&P)[8], int q, float rq,
-                                                      uint32_t mq, int amax) {
+__device__ __forceinline__ uint32_t encode_codes(const int (&P)[8], int q, float rq, uint32_t mq) {
+  int big = 0;   // max |P_i| < 512 iff the OR is
+#pragma unroll
+  for (int l = 0; l < 8; ++l) big |= abs(P[l]);
   int v[8];
   v[0] = P[0];
   v[2] = (P[1] - P[0]) >> 1;
@@ -261,7 +256,7 @@ __device__ __forceinline__ uint32_t encode_codes_amax(const int (&P)[8], int q, 
   v[7] = (P[7] - P[0]) >> 1;
   const int rest = -P[1] - P[2] - P[3] + P[4] - P[5] - P[6] - P[7];
   uint32_t w = 0;
-  if (amax < 512) {
+  if (big < 512) {
     // |v| <= 3 * 511 < 1024 q, so u = v + 1024 q lies in [0, 2048 q) and 2048 q < 2^20 / q.
     // Every product is a full-rate 24-bit multiply (u < 2^15, mq < 2^20, |P_0| < 512).
     v[1] = (__mul24(P[0], 5) + rest) >> 2;
@@ -279,13 +274,6 @@ __device__ __forceinline__ uint32_t encode_codes_amax(const int (&P)[8], int q, 
     for (int l = 0; l < 8; ++l) w |= (uint32_t)mod_q_general(v[l], q, rq) << (4 * l);
   }
   return w;
-}
-
-__device__ __forceinline__ uint32_t encode_codes(const int (&P)[8], int q, float rq, uint32_t mq) {
-  int big = 0;
-#pragma unroll
-  for (int l = 0; l < 8; ++l) big |= abs(P[l]);
-  return encode_codes_amax(P, q, rq, mq, big);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -359,31 +347,6 @@ __device__ __forceinline__ void decode_word_m16(uint32_t w, uint32_t& xa, uint32
   const int r0 = d8 ? (g0 ? f0 - 32 : f0) : f0 - 16;
   const bool fix = d8 ? (odd1 != 0) : (pi != 0);
   x0 = r0 + (fix ? ((g0 == d8) ? 32 : -32) : 0);
-}
-
-// One thread per block of a rows x nb grid of blocks, 256 threads per workgroup: rows
-// shorter than 256 blocks are packed (a power-of-two group of lanes per row), longer rows
-// are cut into 256-block segments.  lg = log2 of the group size (for nb <= 256) or -1.
-// The workgroup's first row rb is uniform; the thread's row is rb + lr and its block j, so
-// per-thread offsets inside the workgroup's rows fit 32 bits.
-struct GridPos {
-  int64_t rb;
-  int lr, j;
-};
-__device__ __forceinline__ GridPos grid_block(int nb, int lg) {
-  GridPos g;
-  if (lg >= 0) {
-    g.rb = (int64_t)blockIdx.x * (256 >> lg);
-    g.lr = (int)(threadIdx.x >> lg);
-    g.j = (int)(threadIdx.x & ((1u << lg) - 1u));
-  } else {
-    const uint32_t segs = ((uint32_t)nb + 255u) / 256u;
-    const uint32_t row = blockIdx.x / segs;
-    g.rb = row;
-    g.lr = 0;
-    g.j = (int)(blockIdx.x - row * segs) * 256 + (int)threadIdx.x;
-  }
-  return g;
 }
 
 // The multiple m of base for beta index idx (0..3): byte idx of the operand's table.

@@ -127,18 +127,14 @@ __global__ __launch_bounds__(256) void tiles_pair_kernel(TileTask a, TileTask w,
   }
 }
 
-// Zero blocks of a tile: the flat range [first, first + count) when cols == 0, else the
-// blocks nb..nb_p-1 of rows 0..rows-1 (cols = nb_p - nb of them per row).
+// Zero blocks nb..nb_p-1 of each row of a tile (cols = nb_p - nb of them; count = rows * cols).
 __global__ __launch_bounds__(256) void tiles_pad_kernel(void* __restrict__ ws, int eb,
-                                                        int64_t first, int64_t count, int nb,
-                                                        int nb_p, int cols) {
+                                                        int64_t count, int nb, int nb_p,
+                                                        int cols) {
   const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (t >= count) return;
-  int64_t g = first + t;
-  if (cols > 0) {
-    const int64_t r = t / cols;
-    g = r * nb_p + nb + (t - r * cols);
-  }
+  const int64_t r = t / cols;
+  const int64_t g = r * nb_p + nb + (t - r * cols);
   if (eb == 16) {
     reinterpret_cast<u32x4*>(ws)[g] = u32x4{0u, 0u, 0u, 0u};
   } else {
@@ -146,18 +142,11 @@ __global__ __launch_bounds__(256) void tiles_pad_kernel(void* __restrict__ ws, i
   }
 }
 
-hipError_t launch_tiles_pad(int et, void* ws, int64_t rows, int nb, int64_t rows_p, int nb_p,
-                            hipStream_t st) {
-  const int eb = et == ET_I8 ? 8 : 16;
-  if (rows_p > rows) {
-    const int64_t count = (rows_p - rows) * nb_p;
-    hipLaunchKernelGGL(tiles_pad_kernel, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, st,
-                       ws, eb, rows * nb_p, count, nb, nb_p, 0);
-  }
+hipError_t launch_tiles_pad(int et, void* ws, int64_t rows, int nb, int nb_p, hipStream_t st) {
   if (nb_p > nb && rows > 0) {
     const int64_t count = rows * (nb_p - nb);
     hipLaunchKernelGGL(tiles_pad_kernel, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, st,
-                       ws, eb, (int64_t)0, count, nb, nb_p, nb_p - nb);
+                       ws, et == ET_I8 ? 8 : 16, count, nb, nb_p, nb_p - nb);
   }
   return hipGetLastError();
 }

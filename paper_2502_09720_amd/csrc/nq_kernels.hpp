@@ -118,10 +118,9 @@ bool encode_rotates(int cols, int strategy);
 void decode_once_layout(int et, int64_t M, int64_t N, int64_t K, int64_t& w_offset,
                         int64_t& rows_p, int& nb_p);
 
-// Zero the padding of an operand tile written by the fused encoder: rows rows..rows_p-1 and,
-// in the first `rows` rows, blocks nb..nb_p-1.
-hipError_t launch_tiles_pad(int et, void* ws, int64_t rows, int nb, int64_t rows_p, int nb_p,
-                            hipStream_t st);
+// Zero the padding columns of A's tile as the fused encoder leaves it: blocks nb..nb_p-1 of its
+// rows (the rows past them reach no output that is stored and stay as they are).
+hipError_t launch_tiles_pad(int et, void* ws, int64_t rows, int nb, int nb_p, hipStream_t st);
 
 // Small M (skinny): decode A once into a tile, then decode W straight into MFMA operands.
 // stages: bit 0 decodes into the workspace, bit 1 contracts (see nq_matmul_stages); et: the
@@ -183,20 +182,6 @@ constexpr int kBetaFan = 64;
 inline int64_t beta_cost_entries(int m) { return (int64_t)m * (m + 1) / 2 + m; }
 inline int64_t beta_level2_nodes(int64_t n) {
   return (n + kBetaFan * kBetaFan - 1) / (kBetaFan * kBetaFan);
-}
-
-// Launch shape for grid_block: log2 of the lanes per row (-1: 256-block segments) and the
-// number of workgroups.
-inline void grid_shape(int64_t rows, int nb, int& lg, int64_t& wgs) {
-  if (nb <= 256) {
-    lg = 0;
-    while ((1 << lg) < nb) ++lg;
-    const int64_t per = 256 >> lg;
-    wgs = (rows + per - 1) / per;
-  } else {
-    lg = -1;
-    wgs = rows * ((nb + 255) / 256);
-  }
 }
 
 // Decoder kernels by variant: 0 Alg. 2 / Alg. 5, 1 NestQuantM (packed 16-bit), 2 NestQuantM

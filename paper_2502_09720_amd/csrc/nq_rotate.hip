@@ -54,7 +54,9 @@ void rotate_kernel(const T* __restrict__ x, int64_t rows, int n, int64_t ld_x, i
     // n = 28 p: the H_28 factor on the way out.  The outputs of a column go straight to
     // memory (64 consecutive columns per wave and store), so nothing is written back to LDS
     // and read again after a barrier (2048 x 14336 bf16: 44.8 us, 51.0 in place; 2048 x
-    // 28672: 102 and 136; a column's outputs dealt to two threads: 48.6).
+    // 28672: 102 and 136; a column's outputs dealt to two threads: 48.6).  n >= 1792 here, so
+    // rr is 1; the indices of the other exits are kept because the compiler makes better code
+    // of them than of one row's alone (46.0 against 47.5 us).
     for (int q = tid; q < rr * p; q += NT) {
       const int r = rr == 1 ? 0 : q / p, b = q - r * p;
       float* __restrict__ o = y + (row0 + r) * ld_y + b;

@@ -57,7 +57,7 @@ hipError_t launch_decode(const uint32_t*, const uint32_t*, const float*, int64_t
                          int, int64_t, const DecodeArgs&, hipStream_t) {
   return rec("decode");
 }
-hipError_t launch_tiles_pad(int, void*, int64_t, int, int64_t, int, hipStream_t) {
+hipError_t launch_tiles_pad(int, void*, int64_t, int, int, hipStream_t) {
   return rec("tiles_pad");
 }
 hipError_t launch_matmul_skinny(int stages, int et, const MatmulOperand&, const MatmulOperand&,
