@@ -371,7 +371,7 @@ int64_t nq_matmul_workspace_size(int64_t M, int64_t N, int64_t K) {
 // every entry point.
 static nq::MatmulOperand operand(const nq_params* p, const uint32_t* codes,
                                  const uint32_t* beta, const float* scales, int64_t rows) {
-  return {codes, beta, scales, p->q, nq::magic_2q(p->q), rows, p->decoder, mult_table(p),
+  return {{codes, beta, scales, p->q, nq::magic_2q(p->q), rows, p->decoder, mult_table(p)},
           nq::tiles_fit_i8(p->q, beta_mult(p, p->k - 1), p->decoder)};
 }
 

@@ -53,7 +53,7 @@ __device__ __forceinline__ u32x4 decode16_dv(uint32_t w, int m, int q, uint32_t 
 }
 
 template <class C, int ET>
-__global__ __launch_bounds__(C::NT, 1) void fused_kernel(MatmulOperand A, MatmulOperand W,
+__global__ __launch_bounds__(C::NT, 1) void fused_kernel(CodedOperand A, CodedOperand W,
                                                          int dva, int dvw, int nb, int tm,
                                                          int tn, float* __restrict__ c,
                                                          int64_t ldc, float scale) {

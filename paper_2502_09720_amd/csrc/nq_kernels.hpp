@@ -69,7 +69,8 @@ struct DecodeArgs {
   double half_beta[4];  // fl64(t * base) / 2 (exact halving), t = 1..4
 };
 
-struct MatmulOperand {
+// A coded operand as the product's kernels take it.
+struct CodedOperand {
   const uint32_t* codes;
   const uint32_t* beta;
   const float* scales;
@@ -78,6 +79,11 @@ struct MatmulOperand {
   int64_t rows;
   int decoder;
   uint32_t mtab;   // byte i: the multiple m of base for beta index i (beta = m * base)
+};
+
+// The same for the launchers, with what chooses among them (kept out of the kernels' argument:
+// eight bytes more there cost the 64 x 64 direct product 5%).
+struct MatmulOperand : CodedOperand {
   bool fits_i8;    // every m X2 of the betas in use fits int8 (tiles_fit_i8)
 };
 

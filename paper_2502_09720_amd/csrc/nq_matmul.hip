@@ -54,7 +54,7 @@ void launch_tiles(const MatmulOperand& X, int nb, int64_t rows_p, int nb_p, void
 // The column's sum is the lanes' sum over the four K quarters and the waves.
 template <int MT, int ET, int DVW, int NWV, bool ADEC = false, bool DOT = false>
 __global__ __launch_bounds__(NWV * 64) void skinny_kernel(const u32x4* __restrict__ ta, int kcb,
-                                                          MatmulOperand A, MatmulOperand W,
+                                                          CodedOperand A, CodedOperand W,
                                                           int nb, float* __restrict__ c,
                                                           int64_t ldc, float scale) {
   constexpr bool I8 = ET == ET_I8;
