@@ -30,7 +30,8 @@ TYPES = {   # q, k, mult, decoder
 
 
 DIRECT = [
-    (1, 64, 136), (100, 1000, 264),                           # 64x64
+    (16, 1000, 264), (33, 1024, 136),                         # 64x64
+    (1, 64, 136), (100, 1000, 264),                           # 64x128 (100 rows in f16: 64x64)
     (300, 4096, 136), (500, 4090, 72),                        # 64x128
     (600, 4096, 136), (640, 4090, 72),                        # 128x128
     (1500, 4096, 136), (1536, 4090, 72),                      # 256x128
