@@ -2,13 +2,12 @@
 
 * nq_matmul, the product that needs no workspace (each workgroup decodes the code words of
   its own rows into on-chip memory and contracts them there): against the oracle's coded
-  product (Alg. 4 for every pair of rows, exact integer sums) on ragged shapes, both tile
-  configurations (M <= 64 and M > 64), mixed q, both decoders (and the byte decoder at
+  product (Alg. 4 for every pair of rows, exact integer sums) on ragged shapes, mixed q, both decoders (and the byte decoder at
   q = 16) and beta multiples that need fp16 tiles; and bit for bit against nq_matmul_ex
   where the two sum in the same order (M > 64).
 * The 256 x 256 tiles of the decode-once GEMM (bf16, fp16 and int8), which the product
-  selects once there is at least one such tile per CU: M = N near 4096 with a short K,
-  every output of C against the oracle.
+  selects where they fill the 256 CUs: M = N near 4096 with a short K, every output of C
+  against the oracle.
 
 Bar: relative Frobenius error <= 1e-3 and every output within 1e-5 of max |C| (the tiles are
 exact integers, only the fp32 accumulation rounds); for the exact int8 contraction every
@@ -73,7 +72,7 @@ DIRECT_CASES = [
     (200, 1, 1, 8, 14, 14, 4, "full", None, None),
     (201, 16, 14336 // 8, 4096, 14, 14, 4, "full", None, None),      # decode-shaped, 1/8 of N
     (202, 64, 300, 1032, 14, 7, 4, "full", None, None),
-    (203, 65, 129, 72, 14, 14, 4, "full", None, None),               # first M of the big tile
+    (203, 65, 129, 72, 14, 14, 4, "full", None, None),
     (204, 300, 520, 1160, 16, 14, 4, "full", None, None),
     (205, 513, 260, 264, 7, 7, 4, "full", None, None),
     (206, 40, 300, 1024, 16, 16, 4, "m", None, None),                # byte decoder, q = 16
@@ -109,25 +108,27 @@ def test_matmul_no_workspace_strided_output(nq):
 
 
 BIG_TILE_CASES = [
-    # (seed, M, N, K, q, k, mult, int8): >= 256 tiles of 256 x 256, short and ragged K
-    (230, 4096, 4096, 264, 14, 4, None, False),                     # bf16
-    (231, 4000, 3990, 520, 14, 4, None, False),                     # bf16, ragged edges
+    # (seed, M, N, K, q, k, mult, int8[, decoder]): >= 256 tiles of 256 x 256, short and
+    # ragged K
+    (230, 4096, 4096, 264, 14, 4, None, False),                     # int8 by the rule of types
+    (231, 4000, 3990, 520, 14, 4, None, False),                     # the same, ragged edges
     (232, 4096, 4096, 264, 14, 4, (6, 8, 10, 16), False),           # fp16 (2q m_k = 448)
     (233, 4096, 4096, 264, 14, 4, None, True),                      # int8 (2q k = 112)
     (234, 4000, 3990, 1032, 7, 4, None, True),                      # int8, ragged edges
+    (235, 4096, 4096, 264, 16, 4, None, False, "m"),                # bf16 (2q k = 128, "m")
+    (236, 4000, 3990, 1032, 16, 4, None, False, "m"),               # bf16, ragged edges, long K
 ]
 
 
 @pytest.mark.parametrize("case", BIG_TILE_CASES,
                          ids=lambda c: f"{c[1]}x{c[2]}x{c[3]}-q{c[4]}-"
-                                       f"{'i8' if c[7] else ('f16' if c[6] else 'bf16')}")
+                                       f"{'i8' if c[7] else ('f16' if c[6] else ('bf16' if len(c) > 8 else 'rule'))}")
 def test_gemm_256x256_tiles(nq, case):
     import torch
-    seed, M, N, K, q, k, mult, i8 = case
-    a, w, C = _coded_pair(seed, M, N, K, q, q, k, "full", mult, mult)
+    seed, M, N, K, q, k, mult, i8 = case[:8]
+    a, w, C = _coded_pair(seed, M, N, K, q, q, k, *case[8:] or ("full",), mult, mult)
     mp, np_ = -(-M // 256) * 256, -(-N // 256) * 256
-    big, mid = (mp // 256) * (np_ // 256), (mp // 256) * (np_ // 128)
-    assert big >= 256 and 2 * -(-big // 256) <= -(-mid // 256)   # the big tile is selected
+    assert (mp // 256) * (np_ // 256) == 256            # one 256 x 256 tile per CU: selected
     got = nq.matmul(a, w, int8=i8)
     torch.cuda.synchronize()
     _check(got, C, exact_int=i8)

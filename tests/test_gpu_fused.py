@@ -7,7 +7,7 @@ exact integer tiles with the same kernel; and the product must meet the usual or
 (relative Frobenius error <= 1e-3).  Cases cover both product paths (M <= 64 and above),
 padding of M and K, fp32 / fp16 / bf16 inputs, both decoders, beta multiples on fp16 tiles,
 Opt-beta, the int8 contraction, streamed long rows, zero rows, and the launch that also
-carries W's tile decode (rows of 257..2048 blocks, M > 64) with every tile type and decoder.
+carries W's tile decode (rows of 257..1024 blocks, M > 64) with every tile type and decoder.
 """
 
 import numpy as np
@@ -48,8 +48,8 @@ FUSED_CASES = [
     (8, 16, 100, 4096, "bf16", "t4", 7, 4, None, 1, 0, True),
     (9, 2, 33, 8, "f32", "normal", 14, 4, None, 0, 0, False),
     (10, 64, 128, 128, "bf16", "normal", 12, 3, (2, 5, 9), 1, 1, False),
-    # rows of 257..2048 blocks with M > 64: W's tile decode rides in the encoder's launch,
-    # for every tile type and decoder variant
+    # rows of 257..1024 blocks with M > 64: W's tile decode rides in the encoder's launch,
+    # for every tile type and decoder variant (and apart from it for longer rows)
     (11, 300, 200, 2056, "bf16", "t4", 14, 4, None, 0, 0, False),
     (12, 130, 77, 4104, "f16", "normal", 16, 4, None, 1, 0, False),
     (13, 96, 300, 3000, "bf16", "t4", 16, 4, (6, 8, 10, 15), 0, 0, False),
@@ -58,7 +58,7 @@ FUSED_CASES = [
     (16, 80, 50, 8192, "bf16", "t4", 7, 3, (1, 2, 4), 1, 0, True),
     (17, 100, 90, 2560, "bf16", "normal", 16, 3, None, 1, 0, True),
     (18, 70, 40, 4096, "f16", "t4", 16, 4, (5, 9, 20, 40), 1, 0, False),
-    # rows of 1025..2048 blocks: W's tile decode workgroups come first in the grid
+    # rows of 1025..2048 blocks: W's tile decode has a launch of its own
     (19, 129, 100, 14336, "bf16", "t4", 14, 4, None, 0, 0, True),
     # more than 1024 rows of 257..512 blocks: two-wave encoder workgroups carry W's decode
     (20, 1100, 96, 4096, "bf16", "t4", 14, 4, None, 0, 0, False),
@@ -111,8 +111,9 @@ def test_encode_matmul_equals_encode_then_matmul(nq, case):
 @pytest.mark.parametrize("K", [1024, 2112])
 def test_encode_matmul_reuses_its_workspace(nq, K):
     """Two calls in a row on one workspace (a larger product, then a smaller one with more
-    padding) give the separate path's results: the padding is cleared on every call (K =
-    2112: W's tile decoded inside the encoder's launch)."""
+    padding) give the separate path's results: the padding columns are cleared on every call,
+    and what padding rows hold reaches no output (K = 2112: W's tile decoded inside the
+    encoder's launch)."""
     import torch
     wstore, _ = workloads.random_rows(600, 300, K, dtype="bf16", scale=0.02)
     w = nq.encode(_dev(wstore, "bf16"), 14, 4)

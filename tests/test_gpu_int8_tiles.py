@@ -100,3 +100,32 @@ def test_both_products_take_the_same_tiles():
     ex, direct = nq.matmul(*dev), nq.matmul_direct(*dev)
     assert torch.equal(ex, direct)
     assert np.all(np.abs(ex.double().cpu().numpy() - C) <= 4e-7 * np.abs(C))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("decoder", ["full", "m"])
+@pytest.mark.parametrize("M,K", [
+    (1, 43680), (2, 21840),       # the last rows whose points the integer-dot kernel holds
+    (1, 43696), (2, 21848),       # past them: int8 tiles decoded inside the product kernel
+    (1, 49152), (2, 24576),       # the last that fit there
+    (1, 49160), (2, 24584),       # past them: A's tile in the workspace
+])
+def test_long_rows_of_one_and_two(M, K, decoder):
+    """One and two activation rows on both sides of the limits of what a workgroup holds of
+    them.  Every sum is an exact int32 on each path."""
+    import paper_2502_09720_amd as nq
+    N, q, k = 33, 14, 4
+    rng = np.random.default_rng(M + K)
+    base = nestquant.default_base(q, k)
+    ops, dev = [], []
+    for rows in (M, N):
+        c = rng.integers(0, q, (rows, K // 8, 8))
+        t = rng.integers(1, k + 1, (rows, K // 8))
+        r = rng.uniform(0.5, 2.0, rows).astype(np.float32)
+        ops.append((nestquant.integer_tiles(c, t, q, decoder), r))
+        dev.append(upload_coded(layout.pack_codes(c), layout.pack_beta(t), r, rows, K, q, k,
+                                base, 1 if decoder == "m" else 0))
+    (TA, ra), (TW, rw) = ops
+    C = nestquant.product_from_tiles(TA, ra, base, TW, rw, base)
+    g = nq.matmul(*dev).double().cpu().numpy()
+    assert np.all(np.abs(g - C) <= 4e-7 * np.abs(C))

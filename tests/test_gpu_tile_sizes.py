@@ -2,7 +2,7 @@
 and of the product without a workspace (256x128, 128x128, 64x128 and 64x64), picked by how many
 fill the CUs, each with whole and ragged edges, in every element type.
 
-Bar: the codes are drawn over all words and K is short, so every sum stays below 2^24 and is
+Bar: the codes are drawn over all words and every sum stays below 2^24 (checked), so it is
 exact in each type; the rounding of the scales leaves an output within 4e-7 of the oracle's.
 """
 
@@ -22,6 +22,15 @@ SHAPES = [
     (2048, 4096, 72), (1900, 4010, 136),                      # 256x128
     (4096, 4096, 72), (4000, 4090, 64),                       # 256x256
 ]
+# The same tiles with their ring of LDS buffers (two to four stages of 128 int8 or 64 or 32
+# 16-bit values a row) used again: 9 to 11 stages in int8, 18 and more in the 16-bit types.
+LONG = [
+    (65, 64, 1160), (777, 1024, 1408),                        # 64x64
+    (300, 4096, 1160), (384, 4000, 1280),                     # 128x64
+    (1000, 4096, 1160), (1024, 4090, 1280),                   # 128x128
+    (2048, 4096, 1160), (1900, 4010, 1280),                   # 256x128
+    (4000, 4090, 1160),                                       # 256x256
+]
 TYPES = {   # q, k, mult, decoder
     "i8": (14, 4, None, "full"),
     "bf16": (16, 4, None, "m"),
@@ -36,17 +45,18 @@ DIRECT = [
     (600, 4096, 136), (640, 4090, 72),                        # 128x128
     (1500, 4096, 136), (1536, 4090, 72),                      # 256x128
 ]
+DIRECT_LONG = [(16, 1000, 1160), (300, 4096, 1160), (600, 4096, 1160), (1500, 4096, 1160)]
 
 
 @pytest.mark.parametrize("et", list(TYPES))
-@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("shape", SHAPES + LONG, ids=lambda s: "x".join(map(str, s)))
 def test_tile_sizes(shape, et):
     import paper_2502_09720_amd as nq
     _check(nq.matmul, shape, et)
 
 
 @pytest.mark.parametrize("et", list(TYPES))
-@pytest.mark.parametrize("shape", DIRECT, ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("shape", DIRECT + DIRECT_LONG, ids=lambda s: "x".join(map(str, s)))
 def test_direct_tile_sizes(shape, et):
     import paper_2502_09720_amd as nq
     _check(nq.matmul_direct, shape, et)
