@@ -253,9 +253,8 @@ int64_t nq_matmul_workspace_size(int64_t M, int64_t N, int64_t K);
  * into the product's workspace, so A is never decoded in a separate pass.  W is decoded as in
  * nq_matmul_ex; for M > 64 and First-beta rows of 2056..8192 entries that decode runs in
  * the encoder's launch, after its workgroups.  Results are those of nq_encode followed by
- * nq_matmul_ex (with
- * NQ_CONTRACT_INT8 in flags, of nq_matmul_stages with that flag; with NQ_ROTATE_A, of
- * nq_rotate_encode in place of nq_encode).
+ * nq_matmul_ex (with NQ_CONTRACT_INT8 in flags, of nq_matmul_stages with that flag; with
+ * NQ_ROTATE_A, of nq_rotate_encode in place of nq_encode).
  *   flags    0, or NQ_CONTRACT_INT8 and / or NQ_ROTATE_A (the widths and strategy of
  *            nq_rotate_encode, else NQ_ERR_UNSUPPORTED);
  *   x, x_dtype, M (rows), K (cols), ld_x, a_codes, a_beta, a_scales: as nq_encode with pa;

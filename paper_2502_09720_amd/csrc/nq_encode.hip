@@ -2,10 +2,11 @@
 // App. F).
 //
 // One lane per 8-entry block.  A row is handled by a group of LANES lanes (a power of two,
-// 8 <= LANES <= 1024): several rows share a 256-thread workgroup when LANES <= 64, and a
-// workgroup is exactly one row when LANES > 64.  Each lane keeps BPT blocks in registers, block
-// j = lane + i * LANES, so the row is read from HBM exactly once and consecutive lanes read
-// consecutive 8-entry blocks (16 B for bf16/fp16, 32 B for fp32).
+// 8 <= LANES <= 1024), lane l its blocks l + i * LANES, so that consecutive lanes read
+// consecutive 8-entry blocks (16 B for bf16/fp16, 32 B for fp32).  encode_wave_kernel
+// (First-beta, rows of up to 2048 blocks) works on slots of 64 blocks a wave, described
+// below; encode_kernel (longer rows, and Opt-beta) gives a row of up to 64 lanes a share of a
+// 256-thread workgroup and a longer one a workgroup, its blocks in registers (BPT) or streamed.
 //
 // Row scale (Alg. 3, s / sqrt(n)): r is the fp32 number nearest to sqrt(sum x^2 / n).  The
 // squares of fp32 values are exact in fp64; the fp64 sum is accepted when it cannot straddle
@@ -338,7 +339,8 @@ __device__ __forceinline__ void opt_block(const float (&v)[8], const float (&c)[
       decode_word_b8<false>(w, a.q, a.m2q, xs[0], xs[1]);
     }
     // a select chain, not an indexed read of the argument block (a memory load); halved here,
-    // exactly (base > 2^-21), instead of after each of the eight products
+    // exactly (base > 2^-21), instead of after each of the eight products (4096 x 4096 bf16
+    // 102.8 -> 101.4 us, 16384 x 8192 738 -> 727)
     const double hb =
         0.5 * (t == 0 ? a.beta[0] : (t == 1 ? a.beta[1] : (t == 2 ? a.beta[2] : a.beta[3])));
     double err = 0.0;
@@ -546,7 +548,7 @@ __global__ __launch_bounds__(LANES > 64 ? LANES : 256) void encode_kernel(
 // and the exact path where the byte form declines.
 // Two-bit beta indices are staged in LDS and packed into words at the end.
 //
-// What bounds it: vector instructions, 1.09 per CU clock at 2^21 x 128 fp16 (382 us; 477 per
+// What bounds it: vector instructions, 1.1 per CU clock at 2^21 x 128 fp16 (385 us; 477 per
 // wave of 64 blocks, of which phase 1 takes 300; a build of 644 took 507 us).  There, one-wave
 // workgroups meet no barrier (462 -> 406 us: four waves waited while one finished the
 // workgroup's queue, a third of the time), unstaged blocks leave LDS for twice the waves, and

@@ -2,13 +2,13 @@
 // words of its own A and W rows straight into LDS as m * X2 tiles and contracts them there.
 //
 // C = A_hat W_hat^T is Alg. 4 of the NestQuant paper for every pair of rows.  Here Alg. 2
-// (with Alg. 5) runs inside the product: for each stage of 8 blocks (64 values of K) the
-// threads of a workgroup fetch the code and beta words of the tile's BM + BN rows, decode
-// them into int8 (or bf16, fp16) integers m * X2, exact, and store them in LDS with the swizzle of
-// the decode-once GEMM; the waves then multiply the stage on 32x32x16 matrix cores with fp32
-// accumulation, and the epilogue scales by r_Ai r_Wj base_A base_W / 4.  Two LDS buffers:
-// stage s + 1 is decoded while stage s is multiplied, and the code words of stage s + 2 are
-// in flight meanwhile.
+// (with Alg. 5) runs inside the product: for each stage of 128 bytes a row (16 blocks as int8,
+// 8 as bf16 or fp16) the threads of a workgroup fetch the code and beta words of the tile's
+// BM + BN rows, decode them into integers m * X2, exact, and store them in LDS with the
+// swizzle of the decode-once GEMM; the waves then multiply the stage on 32x32 matrix cores
+// (int32 sums of int8, fp32 sums of the 16-bit types), and the epilogue scales by
+// r_Ai r_Wj base_A base_W / 4.  Two LDS buffers: stage s + 1 is decoded while stage s is
+// multiplied, and the code words of stage s + 2 are in flight meanwhile.
 //
 // The price of needing no memory: a block of A is decoded once per BN columns of C and a
 // block of W once per BM rows, where the decode-once path (nq_matmul_ex) decodes each block
@@ -16,7 +16,7 @@
 // cores spend on the block, so this path is bound by its decodes.  Rows of the tile past M
 // (or N) are never decoded (their LDS rows stay zero) and waves whose rows all lie past M
 // skip their matrix-core work, which keeps decode-shaped products (M <= 64) cheap: there W
-// is decoded once and A once per BN columns.
+// is decoded once and A once per BN columns.  The tile is pick_direct's.
 #include <algorithm>
 #include <type_traits>
 

@@ -8,16 +8,18 @@
 //
 //   1. tiles_pair_kernel (both operands in one launch; tiles_kernel for one): Alg. 2 on
 //      every code word; writes m * X2 (beta = m * base) into a K-contiguous workspace tile,
-//      zero-padded to the GEMM tile grid: as int8 where every m X2 of both operands fits
-//      (tiles_fit_i8; the uniform grid up to q = 15, and q = 16 with the full decoder), else
-//      as bf16 (|m X2| <= 256) or fp16 (to 2048).  The workspace (a few tens of MB) stays in
-//      the 256 MB Infinity Cache.
+//      its rows zero-padded to whole stages, and zero rows up to the GEMM tile grid (the
+//      fused encoder writes A's rows alone: rows past M reach no stored output): as int8
+//      where every m X2 of both operands fits (tiles_fit_i8; the uniform grid up to q = 15,
+//      and q = 16 with the full decoder), else as bf16 (|m X2| <= 256) or fp16 (to 2048).
+//      The workspace (a few tens of MB) stays in the 256 MB Infinity Cache.
 //   2. gemm_kernel: MFMA GEMM (C = T_A T_W^T; int32 or fp32 accumulation) with the epilogue
 //      C_ij = acc * r_Ai * r_Wj * base_A * base_W / 4.
 //
-// GEMM tiling (gfx950): a workgroup of NW = WM x WN waves owns a BM x BN tile of C; each
-// wave owns (BM/WM) x (BN/WN) as v_mfma_f32_32x32x16_bf16 tiles.  K advances 64 or 32 bf16
-// (SB = 128 or 64 B per row) per stage through NSTAGE LDS buffers filled by
+// GEMM tiling (gfx950): a workgroup of NW = WM x WN waves owns a BM x BN tile of C (pick_tile);
+// each wave owns (BM/WM) x (BN/WN) as 32x32 matrix-core tiles (v_mfma_i32_32x32x32_i8, or the
+// f32_32x32x16 forms of bf16 and fp16).  K advances 128 or 64 bytes of a row (SB: 128 or 64
+// int8, half as many 16-bit values) per stage through NSTAGE LDS buffers filled by
 // global_load_lds_dwordx4: each wave instruction moves 1 KiB of rows straight into LDS (no
 // register staging).  The
 // 16-byte chunk c of row r is stored at chunk c ^ swz(r) (see swz), so that the fragment
@@ -56,8 +58,8 @@ struct Cfg {
   static_assert(NSTAGE * STAGE_BYTES <= 160 * 1024, "LDS is 160 KB");
 };
 
-// 256 x 128 tiles (one per CU for the 8B prefill shapes) and 256 x 256 tiles (half the
-// global->LDS traffic per flop, for products with at least one tile per CU).  LDS holds two
+// 256 x 128 tiles (one per CU for the 8B q_proj prefill) and 256 x 256 tiles (half the
+// global->LDS traffic per operation, for products with about a tile per CU).  LDS holds two
 // stages of the big tile with 128 bytes of K per row, or four with 64 bytes; the deeper
 // prefetch of the latter is faster (with two, waves waited on their loads 45% of the time).
 // The int8 contraction (half the MFMA time per byte) keeps the two 128-byte stages, which
@@ -223,8 +225,8 @@ __global__ __launch_bounds__(C::NW * 64, 1) void gemm_kernel(
 
   // Row and column scales of this lane's outputs.  32x32 accumulator layout: lane l holds
   // column l % 32; register e holds row 8 (e / 4) + 4 (l / 32) + (e % 4).  Indices are
-  // clamped into range (M, N >= 1).  The 256 x 128 tile fetches them before the main loop,
-  // so that the epilogue issues only stores; the 256 x 256 tile's accumulators and
+  // clamped into range (M, N >= 1).  Tiles of up to 128 columns fetch them before the main
+  // loop, so that the epilogue issues only stores; the 256 x 256 tile's accumulators and
   // fragments leave no room to hold them through the loop (they were spilled to scratch and
   // reloaded in every stage), so it fetches them after the loop.
   constexpr bool EARLY_SCALES = BN <= 128;

@@ -47,7 +47,7 @@ struct EncodeArgs {
   double beta[4];  // fl64(m_t * base), t = 1..4
   // Fused encode-and-multiply: when tiles is set, the decoded tile m_t * X2 of every block
   // is also written to tiles[row * nb_p + j] as the product's decode stage would (ElemType
-  // tile_et: 16 B per block for bf16 / fp16, 8 B for int8; mtab as in MatmulOperand).
+  // tile_et: 16 B per block for bf16 / fp16, 8 B for int8; mtab as in CodedOperand).
   void* tiles;
   int tile_et;
   int nb_p;
@@ -88,7 +88,7 @@ struct MatmulOperand : CodedOperand {
 };
 
 // Element type of the decoded tiles m * X2 and of the matrix-core instructions: bf16 holds
-// every integer up to 256, fp16 up to 2048, int8 up to 127 (all exact).
+// every integer of size up to 256, fp16 up to 2048, int8 those of [-128, 127] (all exact).
 enum ElemType { ET_BF16 = 0, ET_F16 = 1, ET_I8 = 2 };
 
 // Whether every m X2 of an operand fits int8.  A decoded point lies in the closed cell

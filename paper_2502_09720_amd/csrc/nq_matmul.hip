@@ -4,14 +4,14 @@
 //
 // Here the weight decode dominates (the product is a few flops per decoded weight entry),
 // so every block of W is decoded exactly once, straight into a matrix-core operand: for
-// v_mfma_f32_16x16x32_bf16 the B operand of lane l is the 8 K-values of column l % 16 at
-// K offset 8 (l / 16), i.e. exactly one decoded block (m * X2, exact in bf16; fp16 for beta
-// sets whose multiples m exceed what bf16 holds), so each lane decodes its own block and no
-// LDS staging is needed.  The activation (at most 64 rows) is
-// decoded once beforehand into a bf16 tile (tiles_kernel) that stays in cache; its
-// fragments are loaded per step for up to four 16-row M tiles.  A workgroup owns 16
-// columns of C; its four waves split K and combine their partial sums through LDS before
-// the epilogue C_ij = acc * r_Ai * r_Wj * base_A * base_W / 4.
+// v_mfma_i32_16x16x64_i8 the B operand of lane l is the 16 K-values of column l % 16 at K
+// offset 16 (l / 16), i.e. two decoded blocks (m * X2 as int8 where every one of both operands
+// fits; else one block of bf16, or of fp16 for multiples beyond bf16's exact integers, for
+// v_mfma_f32_16x16x32), so each lane decodes its own blocks and no LDS staging is needed.
+// The activation (at most 64 rows) is decoded once beforehand into a tile (tiles_kernel) that
+// stays in cache; its fragments are loaded per step for up to four 16-row M tiles.  A
+// workgroup owns 16 columns of C; its eight waves split K and combine their partial sums
+// through LDS before the epilogue C_ij = acc * r_Ai * r_Wj * base_A * base_W / 4.
 #include <algorithm>
 #include <type_traits>
 
@@ -30,7 +30,7 @@ void launch_tiles(const MatmulOperand& X, int nb, int64_t rows_p, int nb_p, void
 
 // One workgroup per 16 columns of C; its NWV waves split K.  An MFMA sums over its K values
 // in any order as long as both operands follow it, so K is dealt in chunks of 4 PD steps'
-// worth of blocks (32 blocks for bf16, PD = 8) and lane (column l % 16, group g = l / 16)
+// worth of blocks (32 blocks of bf16 at PD = 8, or of int8 at PD = 4) and lane (column l % 16, group g = l / 16)
 // takes the g-th quarter of each chunk, one block (bf16, v_mfma_f32_16x16x32_bf16) or two
 // (int8, v_mfma_i32_16x16x64_i8) per step.  A lane's code words of a chunk are then
 // contiguous (two or four 16-byte loads) and share one beta word, and its A fragments are
